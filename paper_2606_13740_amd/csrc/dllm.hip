@@ -147,6 +147,8 @@ namespace {
 
 enum GemmKind { G_QKV = 0, G_RES = 1, G_GU = 2, G_LM = 3 };
 
+int kc_of(int wt) { return wt == WT_F32 ? 16 : (wt == WT_BF16 ? 32 : 64); }
+
 int pick_MT(int M) {
     if (M <= 16) return 1;
     if (M <= 32) return 2;
@@ -174,8 +176,8 @@ struct Decomp {
     bool small;   // 1 tile per workgroup of 4 waves, K over the waves
     int tpg;      // row tiles per wave group
     int ks;       // split-K slices (residual projections)
-    bool wide = false;   // long prompts: whole-K waves of 8 row tiles (WIDE_TILES)
-    bool tiled = false;  // 256+ rows: gemm_tiled_kernel (LDS-staged tiles; tiled_layout)
+    int rt = 0, tt = 0;  // > 64 rows: gemm_tiled_kernel with rt x tt tiles per workgroup (tiled_plan)
+    bool tiled() const { return rt > 0; }
 };
 
 constexpr int N_CU = 256;
@@ -185,56 +187,43 @@ constexpr int N_CU = 256;
 // stages where the 6-tile template runs 3, so the LLaDA-8B widths keep the 6-tile one.
 constexpr int GU_WIDE_TILES = 10;
 
-// bf16 and int8 GEMMs over 256 or more token rows (prompts, wide windows) except the
-// LM head run the LDS-tiled kernel when it gives the chip at least TILED_MIN_WG
-// workgroups: every weight and activation chunk is fetched once per 256-row x 256-token
-// tile (int8: 128 tokens) and shared by the workgroup's waves (LLaDA-8B bf16 at 512
-// rows: gate/up 201 against 276 us, down 107 against 173; at 4096 rows gate/up 1063
-// against 2825, QKV 823 against 1735).  With fewer workgroups the streaming layouts
-// win (QKV at 512 rows, 96 tiles: 238 against 201 us; every GEMM of a 256-row
-// window), except that bf16 QKV of up to 682 rows splits K in two when that reaches
-// TILED_MIN_WG (tiled_ks; LLaDA-8B at 512 rows: 192 workgroups, 192 -> 117 us per
-// layer with the split_epilogue_kernel finish).  Models below the streaming
-// layouts' thresholds (test sizes) take it whenever it applies: it accepts any row
-// and token tile counts (ragged tiles are clamped).  The residual projections split
-// K until the chip holds ~256 workgroups (O/down at 512 rows: 32 tiles x 8 slices);
-// their partial buffer holds min(8 x rows, 4096) rows.  int8 weights take it for QKV
-// only: every wave widens the int8 chunks it reads from LDS, four times over per
-// chunk, which makes the larger projections VALU-bound (4096 rows: QKV 1460 -> 1118
-// us, but gate/up 1799 -> 1984 and down 855 -> 1086 against the whole-K layout).
-constexpr int TILED_MIN_WG = 192;
-bool tiled_layout(GemmKind k, int wt, int Mc) {
-    return Mc >= 256 && ((wt == WT_BF16 && k != G_LM) || (wt == WT_I8 && k == G_QKV));
-}
-// token tiles per workgroup of the tiled kernel
-int tiled_tt(int wt) { return wt == WT_I8 ? TiledShape<WT_I8>::TT : TiledShape<WT_BF16>::TT; }
-int tiled_ks(GemmKind k, int wt, int n_tiles, int Mc) {
-    const long wgs = (long)ceil_div(n_tiles, 16) * ceil_div(Mc / 16, tiled_tt(wt));
-    if (k == G_QKV) {
-        // bf16 QKV of short prompts: two K slices when one leaves fewer than
-        // TILED_MIN_WG workgroups and two fit the chip (LLaDA-8B at 512 rows: 96 -> 192),
-        // finished by split_epilogue_kernel; two slices of an output at most 3 d wide
-        // fit the partial buffer up to 682 rows
-        return (wt == WT_BF16 && wgs < TILED_MIN_WG && 2 * wgs <= N_CU && 6 * Mc <= 4096) ? 2 : 1;
+// Every GEMM over more than 64 token rows (prompts, wide windows) except the LM head and
+// those of fp32 models runs the LDS-tiled kernel: each weight and activation chunk is
+// fetched once per workgroup and shared by its waves, where the streaming layouts re-read
+// the activations per row group and the weights per 64 rows.
+//
+// Which rt x tt tiles a workgroup takes, and how many K slices, is the cheapest of the
+// shapes below under a model of the launch: rounds of workgroups over the chip, each of
+// `steps` 32-column steps that cost a fixed part (barrier, LDS latency) and a part per
+// 16 x 16 tile, plus the partial sums that K slices write and the finish reads.  In units
+// of 4.2 ns, measured (bf16, one round): a step of 16 x 16 tiles 1.29 us, 12 x 16 1.17,
+// 16 x 8 0.79, 12 x 8 0.67, 8 x 8 0.48 alone on a CU and 0.89 for two (its 80 KiB of LDS
+// let two workgroups share one).  int8 and Q4_0 steps take longer in the same proportion.
+// It picks, at the LLaDA-8B widths, 16 x 16 at 4096 rows, 12 x 16 for gate/up at 512
+// rows (256 workgroups in one round, 149 us; 16 x 16 fills 192 CUs: 166), 12 x 8 for
+// gate/up at 200 rows (86 us; 16 x 16: 168), K slices for O and down.
+struct TiledPlan { int rt, tt, ks; };
+TiledPlan tiled_plan(GemmKind k, int n_tiles, int steps, int m_tiles, long rows, size_t part_floats) {
+    static constexpr int shapes[][2] = {{16, 16}, {12, 16}, {16, 8}, {12, 8}, {8, 8}};
+    TiledPlan best{16, 16, 1};
+    double best_cost = 1e30;
+    for (const auto& sh : shapes) {
+        const int rt = sh[0], tt = sh[1];
+        for (int ks = 1; ks <= (k == G_GU ? 1 : 8) && ks <= steps; ks *= 2) {
+            const double out = (double)n_tiles * 16 * rows;          // outputs (padded rows)
+            if (ks > 1 && out * ks > (double)part_floats) break;
+            const long wgs = (long)ceil_div(n_tiles, rt) * ks * ceil_div(m_tiles, tt);
+            double step = 60 + rt * tt;
+            long rounds = ceil_div(wgs, N_CU);
+            if (rt * tt == 64 && wgs > N_CU) { rounds = ceil_div(wgs, 2 * N_CU); step = 212; }
+            // O / down write and read their sums whatever ks is; QKV only with K slices.
+            // 8 bytes per partial value at ~4 TB/s; ~4 us of start and epilogue per round.
+            const int slices = k == G_RES ? ks : (ks > 1 ? ks + 1 : 0);
+            const double cost = rounds * (ceil_div(steps, ks) * step + 1000) + slices * out * 8 / 4e6 / 4.2e-3;
+            if (cost < best_cost) { best_cost = cost; best = TiledPlan{rt, tt, ks}; }
+        }
     }
-    if (k != G_RES) return 1;
-    int ks = 1;
-    while (ks < 8 && wgs * ks * 2 <= N_CU && (long)ks * 2 * Mc <= 4096) ks *= 2;
-    return ks;
-}
-
-// More than 8 token blocks of 64 rows (prompts past 512 tokens, bf16 / int8
-// weights), gate/up and O/down: each wave takes 8 row tiles over the whole K range,
-// 4 row groups per workgroup sharing one token block.  The K-sliced layouts
-// re-stream every row group's weights once per token block and reach ~290 TFLOP/s
-// there; this one holds 8 x 4 tiles of accumulators per wave (LLaDA-8B, int8, 4096
-// rows: gate/up 1980 -> 1817 us, down 1156 -> 859 us, O 462 -> 371 us).  QKV keeps
-// its layout: with 2 row groups per workgroup (its RoPE staging needs the LDS) the
-// epilogue over 128 rows x 64 tokens on 128 threads made it slower (1521 -> 1688 us).
-// Up to 8 blocks the K-sliced layouts with the XCD-aware block order are faster.
-constexpr int WIDE_TILES = 8;
-bool wide_layout(GemmKind k, int wt, int gy) {
-    return gy > 8 && (k == G_GU || k == G_RES) && (wt == WT_BF16 || wt == WT_I8);
+    return best;
 }
 
 // Row tiles per wave group of each template at mt token tiles.  Q4_0 exceptions:
@@ -255,22 +244,23 @@ constexpr int template_fw(GemmKind k, int wt, int mt) {
 }
 int template_nwn(GemmKind k) { return k == G_LM ? 4 : 1; }
 
-Decomp decomp(GemmKind k, int wt, int n_tiles, int Mc, int gy) {
-    const int min_tiles = (k == G_QKV || k == G_RES) ? 128 : (k == G_GU ? 256 : 512);
-    if (tiled_layout(k, wt, Mc)) {
-        const int ks = tiled_ks(k, wt, n_tiles, Mc);
-        const long wgs = (long)ceil_div(n_tiles, 16) * ceil_div(Mc / 16, tiled_tt(wt)) * ks;
-        if (n_tiles < min_tiles || wgs >= TILED_MIN_WG) return Decomp{false, 16, ks, false, true};
+// W: the packed operand of M token rows, computed as gy blocks of MT tiles (Mc rows) by
+// the streaming layouts.
+Decomp decomp(GemmKind k, int wt, const PackedW& W, int M, int MT, int gy, size_t part_floats) {
+    const int n_tiles = W.n_tiles, Mc = gy * MT * 16;
+    if (wt != WT_F32 && k != G_LM && M > 64) {
+        const int steps = W.KCw * (kc_of(wt) / 32);
+        const TiledPlan p = tiled_plan(k, n_tiles, steps, ceil_div(M, 16), Mc, part_floats);
+        return Decomp{false, 0, p.ks, p.rt, p.tt};
     }
+    const int min_tiles = (k == G_QKV || k == G_RES) ? 128 : (k == G_GU ? 256 : 512);
     if (n_tiles < min_tiles) return Decomp{true, 1, 1};
-    if (wide_layout(k, wt, gy)) return Decomp{false, WIDE_TILES, 1, true};
-    const int fw = template_fw(k, wt, Mc / (16 * gy)), nwn = template_nwn(k);
+    const int fw = template_fw(k, wt, MT), nwn = template_nwn(k);
     Decomp best{false, 1, 1};
     double best_load = 1e30;
     // bf16 gate/up up to 2 token tiles may also take the 10-tile template
     // (GU_WIDE_TILES), for widths whose row tiles would need two rounds at 6
-    const int mt = Mc / (16 * gy);
-    const int fw_max = (k == G_GU && wt == WT_BF16 && mt <= 2) ? GU_WIDE_TILES : fw;
+    const int fw_max = (k == G_GU && wt == WT_BF16 && MT <= 2) ? GU_WIDE_TILES : fw;
     for (int tpg = fw_max; tpg >= 1; --tpg) {
         for (int ks = (k == G_RES && Mc <= 64) ? RES_SPLIT : 1; ks >= 1; ks >>= 1) {
             const long wgs = (long)ceil_div(ceil_div(n_tiles, tpg), nwn) * ks * gy;
@@ -313,36 +303,49 @@ int launch_gemm_mt(int MT, const GemmArgs& g, const Epi& epi, int n_tiles, int K
 // Number of row groups (LM-head partial records) a launch writes.
 int row_groups(const Decomp& dc, int n_tiles) { return ceil_div(n_tiles, dc.tpg); }
 
+template <int WT, int RT, int TT, class Epi>
+void launch_tiled_inst(const GemmArgs& g, const Epi& epi, int ks, int m_tiles, hipStream_t s) {
+    dim3 grid(ceil_div(g.n_tiles, RT), ks, ceil_div(m_tiles, TT));
+    hipLaunchKernelGGL((gemm_tiled_kernel<WT, RT, TT, Epi>), grid, dim3(512), 0, s, g, epi, m_tiles);
+}
+
+template <int WT, class Epi>
+int launch_tiled(const Decomp& dc, const GemmArgs& g, const Epi& epi, int m_tiles, hipStream_t s) {
+    if (dc.rt == 16 && dc.tt == 16) launch_tiled_inst<WT, 16, 16>(g, epi, dc.ks, m_tiles, s);
+    else if (dc.rt == 12 && dc.tt == 16) launch_tiled_inst<WT, 12, 16>(g, epi, dc.ks, m_tiles, s);
+    else if (dc.rt == 16 && dc.tt == 8) launch_tiled_inst<WT, 16, 8>(g, epi, dc.ks, m_tiles, s);
+    else if (dc.rt == 12 && dc.tt == 8) launch_tiled_inst<WT, 12, 8>(g, epi, dc.ks, m_tiles, s);
+    else if (dc.rt == 8 && dc.tt == 8) launch_tiled_inst<WT, 8, 8>(g, epi, dc.ks, m_tiles, s);
+    else return fail(DLLM_E_INVAL, "internal: no tiled GEMM of this shape");
+    return DLLM_OK;
+}
+
 template <int WT, GemmKind KIND, class Epi>
-int launch_gemm(const Decomp& dc, int n_tiles, int MT, const GemmArgs& g0, const Epi& epi, int gy, hipStream_t s,
+int launch_gemm(const Decomp& dc, int M, int MT, const GemmArgs& g0, const Epi& epi, int gy, hipStream_t s,
                 float* part = nullptr, size_t part_floats = 0) {
     GemmArgs g = g0;
     g.tpg = dc.tpg;
-    if constexpr ((WT == WT_BF16 && KIND != G_LM) || (WT == WT_I8 && KIND == G_QKV)) {
-        if (dc.tiled) {
-            using TS = TiledShape<WT>;
-            const int Mc = gy * MT * 16;
-            if (Mc % 64 != 0) return fail(DLLM_E_INVAL, "internal: tiled GEMM needs 64-row blocks");
-            dim3 grid(ceil_div(n_tiles, TS::RT), dc.ks, ceil_div(Mc / 16, TS::TT));
-            if constexpr (KIND == G_QKV && WT == WT_BF16) {
+    const int n_tiles = g.n_tiles;
+    if constexpr (WT != WT_F32 && KIND != G_LM) {
+        if (dc.tiled()) {
+            const int m_tiles = ceil_div(M, 16);
+            if constexpr (KIND == G_QKV) {
                 if (dc.ks > 1) {
                     // K slices into partial sums, then split_epilogue_kernel sums them and
                     // runs the QKV epilogue (the bias goes in once, after the sum)
-                    const int N = n_tiles * 16;
-                    if (part == nullptr || (size_t)dc.ks * Mc * N > part_floats)
+                    const int N = n_tiles * 16, rows = m_tiles * 16;
+                    if (part == nullptr || (size_t)dc.ks * rows * N > part_floats)
                         return fail(DLLM_E_INVAL, "internal: split-K buffer too small");
-                    GemmArgs gp = g0;
-                    gp.bias = nullptr;
-                    const EpiPartial ep{part, N, Mc};
-                    hipLaunchKernelGGL((gemm_tiled_kernel<WT, EpiPartial>), grid, dim3(512), 0, s, gp, ep, Mc / 16);
-                    hipLaunchKernelGGL((split_epilogue_kernel<Epi>), dim3(ceil_div(n_tiles, 16), ceil_div(Mc / 16, 4)),
-                                       dim3(256), 0, s, (const float*)part, dc.ks, Mc, N, n_tiles, Mc / 16, g0.bias,
+                    g.bias = nullptr;
+                    const EpiPartial ep{part, N, rows};
+                    if (int rc = launch_tiled<WT>(dc, g, ep, m_tiles, s)) return rc;
+                    hipLaunchKernelGGL((split_epilogue_kernel<Epi>), dim3(ceil_div(n_tiles, 16), ceil_div(m_tiles, 4)),
+                                       dim3(256), 0, s, (const float*)part, dc.ks, rows, N, n_tiles, m_tiles, g0.bias,
                                        epi);
                     return DLLM_OK;
                 }
             }
-            hipLaunchKernelGGL((gemm_tiled_kernel<WT, Epi>), grid, dim3(512), 0, s, g0, epi, Mc / 16);
-            return DLLM_OK;
+            return launch_tiled<WT>(dc, g, epi, m_tiles, s);
         }
     }
     if (dc.small) return launch_gemm_mt<WT, -1, 1, 4>(MT, g, epi, n_tiles, dc.ks, gy, s);
@@ -351,13 +354,6 @@ int launch_gemm(const Decomp& dc, int n_tiles, int MT, const GemmArgs& g0, const
             if (g.tpg > GU_WIDE_TILES || MT > 2) return fail(DLLM_E_INVAL, "internal: gate/up tiles outside the templates");
             if (MT == 1) launch_gemm_inst<WT, GU_WIDE_TILES, 1, 8, 1>(g, epi, n_tiles, 1, gy, s);
             else launch_gemm_inst<WT, GU_WIDE_TILES, 1, 8, 2>(g, epi, n_tiles, 1, gy, s);
-            return DLLM_OK;
-        }
-    }
-    if constexpr ((WT == WT_BF16 || WT == WT_I8) && (KIND == G_GU || KIND == G_RES)) {
-        if (dc.wide) {
-            if (MT != 4 || g.tpg != WIDE_TILES) return fail(DLLM_E_INVAL, "internal: wide layout needs 64-row blocks");
-            launch_gemm_inst<WT, WIDE_TILES, 4, 1, 4>(g, epi, n_tiles, 1, gy, s);
             return DLLM_OK;
         }
     }
@@ -477,8 +473,6 @@ size_t ws_carve(const dllm_model* m, int rows, int wrows, size_t part_floats, ch
     return off;
 }
 
-int kc_of(int wt) { return wt == WT_F32 ? 16 : (wt == WT_BF16 ? 32 : 64); }
-
 void plan_packed(PackedW& p, int wt, int N, int K) {
     p.N = N;
     p.K = K;
@@ -569,13 +563,13 @@ template <int WT, bool XF32>
 int residual_proj(dllm_model* m, Workspace& w, const PackedW& W, const void* X, const float* gnext, int M, int Mc,
                   int MT, int gy, hipStream_t s, bool sel = false, const uint8_t* need = nullptr, int n_sel = 0) {
     const int d = m->cfg.d_model;
-    const Decomp dc = decomp(G_RES, WT, W.n_tiles, Mc, gy);
+    const Decomp dc = decomp(G_RES, WT, W, M, MT, gy, w.part_floats);
     const int KS = dc.ks;
     if ((size_t)KS * Mc * d > w.part_floats) return fail(DLLM_E_INVAL, "internal: split-K buffer too small");
     GemmArgs g{W.w, W.scale, X, W.KCw, W.KCw * WTraits<WT>::XPER, W.n_tiles};
     g.qs = W.qs;
     EpiPartial e{w.part, d, Mc};
-    int rc = launch_gemm<WT, G_RES>(dc, W.n_tiles, MT, g, e, gy, s);
+    int rc = launch_gemm<WT, G_RES>(dc, M, MT, g, e, gy, s);
     if (rc) return rc;
 #define RRED(KS_)                                                                                              \
     hipLaunchKernelGGL((residual_reduce_kernel<XF32, KS_>), dim3(Mc), dim3(ROW_NT), 0, s, (const float*)w.part, Mc, \
@@ -684,7 +678,7 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
             if (fused && (l == 0 || FUSE_DOWN)) fold_norm(g, m, w, nssq_qkv(l));
             EpiQKV<XF32> e{d, m->dkv, Dh, a.M, a.pos_base, a.pos, m->rope, (AT*)w.q, q_plane, Kc, Vt, kv->Cs};
             ProbeScope ps(m, DLLM_K_QKV, s);
-            if ((rc = launch_gemm<WT, G_QKV>(decomp(G_QKV, WT, L.qkv.n_tiles, Mc, gy), L.qkv.n_tiles, MT, g, e, gy, s,
+            if ((rc = launch_gemm<WT, G_QKV>(decomp(G_QKV, WT, L.qkv, a.M, MT, gy, w.part_floats), a.M, MT, g, e, gy, s,
                                              w.part, w.part_floats)))
                 return rc;
         }
@@ -777,7 +771,7 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
             if (fused) fold_norm(g, m, w, L.o.n_tiles);
             EpiSwiGLU<XF32> e{w.af, m->KCx_f};
             ProbeScope ps(m, DLLM_K_GATEUP, s);
-            if ((rc = launch_gemm<WT, G_GU>(decomp(G_GU, WT, L.gu.n_tiles, Mc, gy), L.gu.n_tiles, MT, g, e, gy, s)))
+            if ((rc = launch_gemm<WT, G_GU>(decomp(G_GU, WT, L.gu, a.M, MT, gy, 0), a.M, MT, g, e, gy, s)))
                 return rc;
         }
         // down projection + residual (+ next norm operand)
@@ -808,14 +802,14 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
         GemmArgs g{m->lm.w, m->lm.scale, w.xg, m->lm.KCw, m->lm.KCw * WTraits<WT>::XPER, m->lm.n_tiles};
         g.qs = m->lm.qs;
         if (fused && FUSE_DOWN) fold_norm(g, m, w, m->layers[c.n_layers - 1].down.n_tiles);
-        const Decomp dc = decomp(G_LM, WT, m->lm.n_tiles, gyl * MTl * 16, gyl);
+        const Decomp dc = decomp(G_LM, WT, m->lm, Ml, MTl, gyl, 0);
         const int gx = row_groups(dc, m->lm.n_tiles);
         if (gx > m->n_lm_wg) return fail(DLLM_E_INVAL, "internal: LM-head partials exceed their buffer");
         if (Ml > 0) {
             EpiLM e{c.vocab, c.mask_id, Ml, w.lm, w.wrows, a.logits};
             for (int r = 0; r < (a.replay < 0 ? 1 : a.n_replay); ++r) {
                 ProbeScope ps(m, DLLM_K_LMHEAD, s);
-                if ((rc = launch_gemm<WT, G_LM>(dc, m->lm.n_tiles, MTl, g, e, gyl, s))) return rc;
+                if ((rc = launch_gemm<WT, G_LM>(dc, Ml, MTl, g, e, gyl, s))) return rc;
             }
         }
         if (a.replay < 0)

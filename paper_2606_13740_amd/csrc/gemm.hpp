@@ -50,13 +50,37 @@ struct GemmArgs {
 //       first weight loads
 //   void stage(const Pre& p, char* sm, int n0, int nrows, int m0, int mcols) const
 //       stores them to sm once the first weight loads are in flight
-//   template <class SC> void operator()(float* Y, int ldy, int n0, int nrows, int m0, int mcols, int part,
-//                                       char* sm, const SC& sc) const
-// Y is LDS [nrows][ldy] holding the K sums of weight rows [n0, n0 + nrows) for
-// tokens [m0, m0 + mcols); the output of row nl, token ml is sc(Y[nl][ml], nl, ml)
-// (int8 row scale, folded RMSNorm scale, bias).  Every thread of the workgroup calls
-// it (it may use __syncthreads and overwrite Y); `part` numbers the row group for
-// per-group partial results.
+//   template <class YV, class SC> void operator()(YV Y, int n0, int nrows, int m0, int mcols, int part,
+//                                                 char* sm, const SC& sc) const
+// Y views the K sums of weight rows [n0, n0 + nrows) for tokens [m0, m0 + mcols) in LDS;
+// the output of row nl, token ml is sc(Y(nl, ml), nl, ml) (int8 row scale, folded RMSNorm
+// scale, bias).  Every thread of the workgroup calls it (it may use __syncthreads);
+// `part` numbers the row group for per-group partial results; sm is what stage() filled,
+// or nullptr where the kernel staged nothing.
+
+// LDS tile of sums, a row per weight row (streaming kernel: LD odd, so that a wave that
+// walks rows or tokens hits distinct banks).
+template <int LD>
+struct YRows {
+    static constexpr int kUnroll = 1;      // epilogue items a thread has in flight
+    const float* y;
+    __device__ __forceinline__ float operator()(int nl, int ml) const { return y[nl * LD + ml]; }
+    // rows nl .. nl + 3 of one token
+    __device__ __forceinline__ float4 quad(int nl, int ml) const {
+        const float* p = y + nl * LD + ml;
+        return make_float4(p[0], p[LD], p[2 * LD], p[3 * LD]);
+    }
+};
+// The same, a row per token (tiled kernel: a lane's four accumulator rows are one 16-byte
+// store, and the epilogues, which take four or eight rows of a token, read 16 bytes).
+template <int LD>
+struct YTokens {
+    static_assert(LD % 4 == 0, "quads are 16-byte aligned");
+    static constexpr int kUnroll = 4;
+    const float* y;
+    __device__ __forceinline__ float operator()(int nl, int ml) const { return y[ml * LD + nl]; }
+    __device__ __forceinline__ float4 quad(int nl, int ml) const { return *(const float4*)(y + ml * LD + nl); }
+};
 
 // No scales at all (most bf16 launches): the epilogues read the sums unchanged.
 struct NoScale {
@@ -81,6 +105,12 @@ struct YScale {
         return y;
     }
 };
+// four consecutive rows of one token
+template <class YV, class SC>
+__device__ __forceinline__ float4 scaled_quad(const YV& Y, const SC& sc, int nl, int ml) {
+    const float4 v = Y.quad(nl, ml);
+    return make_float4(sc(v.x, nl, ml), sc(v.y, nl + 1, ml), sc(v.z, nl + 2, ml), sc(v.w, nl + 3, ml));
+}
 
 // Loads in flight per wave: as many K chunks as fit in ~128 VGPRs of buffers.
 template <int WT, int F, int MT>
@@ -518,9 +548,9 @@ gemm_kernel(GemmArgs g, Epi epi) {
             if (g.wscale != nullptr) sc.ws = ws_sm[q];
             if (g.ssq != nullptr) sc.rs = rs_sm;
             if (g.bias != nullptr) sc.b = b_sm[q];
-            epi(Y[q], LDY, nt0 * 16, nf * 16, mt0 * 16, MR, bx * NWn + q, esm + q * ESM, sc);
+            epi(YRows<LDY>{Y[q]}, nt0 * 16, nf * 16, mt0 * 16, MR, bx * NWn + q, esm + q * ESM, sc);
         } else {
-            epi(Y[q], LDY, nt0 * 16, nf * 16, mt0 * 16, MR, bx * NWn + q, esm + q * ESM, NoScale{});
+            epi(YRows<LDY>{Y[q]}, nt0 * 16, nf * 16, mt0 * 16, MR, bx * NWn + q, esm + q * ESM, NoScale{});
         }
         __syncthreads();
     }
@@ -552,17 +582,7 @@ struct EpiQKV {
     static constexpr int kPairs = 24 * 64;          // staged (cos, sin): 3 row tiles x 64 tokens
     static constexpr int kSmem = kPairs * 8;
 
-    // one Q value (fp16 hi and lo planes) / one cache value (one fp16 plane)
-    __device__ __forceinline__ static void put_q(T* p, size_t plane, float v) {
-        if constexpr (XF32) {
-            *p = v;
-        } else {
-            uint16_t hi, lo;
-            split_f16(v, hi, lo);
-            p[0] = hi;
-            p[plane] = lo;
-        }
-    }
+    // one cache value (one fp16 plane)
     __device__ __forceinline__ static void put_kv(T* p, float v) {
         if constexpr (XF32) *p = v;
         else *p = f16_sat(v);
@@ -631,97 +651,89 @@ struct EpiQKV {
         }
     }
 
-    template <class SC>
-    __device__ void operator()(float* Y, int ldy, int n0, int nrows, int m0, int mcols, int, char* sm,
-                               const SC& sc) const {
+    template <class YV, class SC>
+    __device__ void operator()(const YV& Y, int n0, int nrows, int m0, int mcols, int, char* sm, const SC& sc) const {
         const int npairs = nrows >> 1;
         const int half = Dh >> 1;
-        const bool staged = npairs * mcols <= kPairs;
+        const bool staged = sm != nullptr && npairs * mcols <= kPairs;
         const float2* csm = (const float2*)sm;
-        if (n0 + nrows <= d + dkv) {
-            // Q / K rows: four consecutive RoPE pairs (dims j..j+3 and j+half..j+half+3) per thread
-            const int nq = npairs >> 2;
-            for (int idx = threadIdx.x; idx < nq * mcols; idx += blockDim.x) {
-                const int qd = idx % nq, ml = idx / nq;
-                const int m = m0 + ml;
-                if (m >= M) continue;
-                const int p0 = 4 * qd, n = n0 + 2 * p0;
-                const int ps = pos ? pos[m] : pos_base + m;
-                const int seg = n < d ? 0 : 1, nn = n - seg * d;
-                const int h = nn / Dh, j0 = (nn - h * Dh) >> 1;
+        const int nqk = max(0, min(nrows, d + dkv - n0));      // Q / K rows of the group, then V rows
+        // Q / K rows: four consecutive RoPE pairs (dims j..j+3 and j+half..j+half+3) per
+        // item; a thread loads the (cos, sin) of all its items of a round before it stores
+        // any (behind a store the compiler cannot tell from the table, each load would wait
+        // for the one before it)
+        const int nq = nqk >> 3, nitems = nq * mcols;
+        constexpr int U = YV::kUnroll;
+        for (int base = threadIdx.x; base < nitems; base += U * blockDim.x) {
+            float2 cs[U][4];
+            int ps[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int idx = base + u * blockDim.x;
+                const int qd = idx % nq, ml = idx / nq, m = m0 + ml, p0 = 4 * qd;
+                ps[u] = -1;
+                if (idx >= nitems || m >= M) continue;
+                ps[u] = pos ? pos[m] : pos_base + m;
+                const int j0 = ((n0 + 2 * p0) & (Dh - 1)) >> 1;      // d and dkv are multiples of Dh (a power of 2)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    cs[u][e] = staged ? csm[p0 + e + npairs * ml] : rope[(size_t)ps[u] * half + j0 + e];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (ps[u] < 0) continue;
+                const int idx = base + u * blockDim.x;
+                const int qd = idx % nq, ml = idx / nq, m = m0 + ml;
+                const int nl = 8 * qd, n = n0 + nl;
+                const bool isq = n < d;
+                const int nn = isq ? n : n - d;
+                const int j0 = (nn & (Dh - 1)) >> 1, head0 = nn & ~(Dh - 1);   // head0: the head's first row
+                const float4 y0 = scaled_quad(Y, sc, nl, ml), y1 = scaled_quad(Y, sc, nl + 4, ml);
+                const float a[4] = {y0.x, y0.z, y1.x, y1.z}, b[4] = {y0.y, y0.w, y1.y, y1.w};
                 float ra[4], rb[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const int na = 2 * (p0 + e);
-                    const float a = sc(Y[na * ldy + ml], na, ml), b = sc(Y[(na + 1) * ldy + ml], na + 1, ml);
-                    const float2 cs = staged ? csm[p0 + e + npairs * ml] : rope[(size_t)ps * half + j0 + e];
-                    ra[e] = a * cs.x - b * cs.y;
-                    rb[e] = a * cs.y + b * cs.x;
+                    ra[e] = a[e] * cs[u][e].x - b[e] * cs[u][e].y;
+                    rb[e] = a[e] * cs[u][e].y + b[e] * cs[u][e].x;
                 }
-                if (seg == 0) {
-                    T* dst = q + (size_t)m * d + h * Dh;
+                if (isq) {
+                    T* dst = q + (size_t)m * d + head0;
                     put4_q(dst + j0, q_plane, ra);
                     put4_q(dst + j0 + half, q_plane, rb);
                 } else {
-                    T* dst = Kc + ((size_t)h * Cs + ps) * Dh;
+                    T* dst = Kc + (size_t)head0 * Cs + (size_t)ps[u] * Dh;
                     put4_kv(dst + j0, ra);
                     put4_kv(dst + j0 + half, rb);
                 }
             }
-            return;
         }
-        if (n0 >= d + dkv && pos == nullptr && ((pos_base + m0) & 3) == 0) {
-            // V^T rows, consecutive positions: four tokens per thread along the row; a
-            // quad that reaches past the last real row falls back to single stores
+        if (nqk >= nrows) return;
+        // V^T rows: rr of the V projection is dim rr % Dh of head rr / Dh, cache row rr
+        const int nv = nrows - nqk, v0 = n0 + nqk - d - dkv;
+        if (pos == nullptr && ((pos_base + m0) & 3) == 0) {
+            // consecutive positions: four tokens per thread along the row; a quad that
+            // reaches past the last real row falls back to single stores
             const int nt = mcols >> 2;
-            for (int idx = threadIdx.x; idx < nrows * nt; idx += blockDim.x) {
-                const int tq = idx % nt, nl = idx / nt;
+            for (int idx = threadIdx.x; idx < nv * nt; idx += blockDim.x) {
+                const int tq = idx % nt, nl = nqk + idx / nt;
                 const int m = m0 + 4 * tq;
                 if (m >= M) continue;
-                const int nn = n0 + nl - d - dkv;
-                const int h = nn / Dh, rr = nn - h * Dh;
-                T* dst = Vt + ((size_t)h * Dh + rr) * Cs + pos_base + m;
-                const float* y = Y + nl * ldy + 4 * tq;
+                T* dst = Vt + (size_t)(v0 + nl - nqk) * Cs + pos_base + m;
+                float v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = sc(Y(nl, 4 * tq + e), nl, 4 * tq + e);
                 if (m + 3 < M) {
-                    const float v[4] = {sc(y[0], nl, 4 * tq), sc(y[1], nl, 4 * tq + 1), sc(y[2], nl, 4 * tq + 2),
-                                        sc(y[3], nl, 4 * tq + 3)};
                     put4_kv(dst, v);
                 } else {
-                    for (int e = 0; e < 4 && m + e < M; ++e) put_kv(dst + e, sc(y[e], nl, 4 * tq + e));
+                    for (int e = 0; e < 4 && m + e < M; ++e) put_kv(dst + e, v[e]);
                 }
             }
             return;
         }
-        // general case (a group across the K/V boundary, or explicit positions)
-        for (int idx = threadIdx.x; idx < npairs * mcols; idx += blockDim.x) {
-            const int p = idx % npairs, ml = idx / npairs;
-            const int m = m0 + ml;
+        for (int idx = threadIdx.x; idx < nv * mcols; idx += blockDim.x) {
+            const int ml = idx % mcols, nl = nqk + idx / mcols, m = m0 + ml;
             if (m >= M) continue;
-            const int n = n0 + 2 * p;
-            const float a = sc(Y[(2 * p) * ldy + ml], 2 * p, ml), b = sc(Y[(2 * p + 1) * ldy + ml], 2 * p + 1, ml);
-            const int ps = pos ? pos[m] : pos_base + m;
-            const int seg = n < d ? 0 : (n < d + dkv ? 1 : 2);
-            const int nn = n - (seg == 0 ? 0 : (seg == 1 ? d : d + dkv));
-            const int h = nn / Dh, rr = nn - h * Dh;
-            if (seg < 2) {
-                const int j = rr >> 1;
-                const float2 cs = staged ? csm[p + npairs * ml] : rope[(size_t)ps * half + j];
-                const float ra = a * cs.x - b * cs.y;
-                const float rb = a * cs.y + b * cs.x;
-                if (seg == 0) {
-                    T* dst = q + (size_t)m * d + h * Dh;
-                    put_q(dst + j, q_plane, ra);
-                    put_q(dst + j + half, q_plane, rb);
-                } else {
-                    T* dst = Kc + ((size_t)h * Cs + ps) * Dh;
-                    put_kv(dst + j, ra);
-                    put_kv(dst + j + half, rb);
-                }
-            } else {
-                T* dst = Vt + ((size_t)h * Dh + rr) * Cs + ps;
-                put_kv(dst, a);
-                put_kv(dst + Cs, b);
-            }
+            put_kv(Vt + (size_t)(v0 + nl - nqk) * Cs + (pos ? pos[m] : pos_base + m), sc(Y(nl, ml), nl, ml));
         }
     }
 };
@@ -737,17 +749,13 @@ struct EpiPartial {
     __device__ void fetch(Pre&, int, int, int, int) const {}
     __device__ void stage(const Pre&, char*, int, int, int, int) const {}
 
-    template <class SC>
-    __device__ void operator()(float* Y, int ldy, int n0, int nrows, int m0, int mcols, int, char*,
-                               const SC& sc) const {
+    template <class YV, class SC>
+    __device__ void operator()(const YV& Y, int n0, int nrows, int m0, int mcols, int, char*, const SC& sc) const {
         float* base = P + (size_t)blockIdx.y * rows * ldn;
         const int nq = nrows >> 2;
         for (int idx = threadIdx.x; idx < nq * mcols; idx += blockDim.x) {
             const int qd = idx % nq, ml = idx / nq, nl = 4 * qd;
-            const float* y = Y + nl * ldy + ml;
-            *(float4*)(base + (size_t)(m0 + ml) * ldn + n0 + nl) =
-                make_float4(sc(y[0], nl, ml), sc(y[ldy], nl + 1, ml), sc(y[2 * ldy], nl + 2, ml),
-                            sc(y[3 * ldy], nl + 3, ml));
+            *(float4*)(base + (size_t)(m0 + ml) * ldn + n0 + nl) = scaled_quad(Y, sc, nl, ml);
         }
     }
 };
@@ -777,8 +785,8 @@ struct EpiResidual {
     __device__ void fetch(Pre&, int, int, int, int) const {}
     __device__ void stage(const Pre&, char*, int, int, int, int) const {}
 
-    template <class SC>
-    __device__ void operator()(float* Y, int ldy, int n0, int nrows, int m0, int mcols, int grp, char*,
+    template <class YV, class SC>
+    __device__ void operator()(const YV& Y, int n0, int nrows, int m0, int mcols, int grp, char*,
                                const SC& sc) const {
         // nrows is 16 (one row tile): 4 quads per token, consecutive threads
         for (int idx = threadIdx.x; idx < 4 * mcols; idx += blockDim.x) {
@@ -788,9 +796,8 @@ struct EpiResidual {
             if (m < M && n < d) {
                 float4* xp = (float4*)(x + (size_t)m * d + n);
                 v = *xp;
-                const float* y = Y + (4 * qd) * ldy + ml;
-                v.x += sc(y[0], 4 * qd, ml); v.y += sc(y[ldy], 4 * qd + 1, ml);
-                v.z += sc(y[2 * ldy], 4 * qd + 2, ml); v.w += sc(y[3 * ldy], 4 * qd + 3, ml);
+                const float4 y = scaled_quad(Y, sc, 4 * qd, ml);
+                v.x += y.x; v.y += y.y; v.z += y.z; v.w += y.w;
                 *xp = v;
                 const float4 gg = *(const float4*)(g + n);
                 u = make_float4(v.x * gg.x, v.y * gg.y, v.z * gg.z, v.w * gg.w);
@@ -818,19 +825,16 @@ struct EpiSwiGLU {
     __device__ void stage(const Pre&, char*, int, int, int, int) const {}
 
     // four consecutive outputs (eight packed rows) per thread
-    template <class SC>
-    __device__ void operator()(float* Y, int ldy, int n0, int nrows, int m0, int mcols, int, char*,
-                               const SC& sc) const {
+    template <class YV, class SC>
+    __device__ void operator()(const YV& Y, int n0, int nrows, int m0, int mcols, int, char*, const SC& sc) const {
         const int nq = nrows >> 3;
         for (int idx = threadIdx.x; idx < nq * mcols; idx += blockDim.x) {
             const int qd = idx % nq, ml = idx / nq;
+            const float4 y0 = scaled_quad(Y, sc, 8 * qd, ml), y1 = scaled_quad(Y, sc, 8 * qd + 4, ml);
+            const float gt[4] = {y0.x, y0.z, y1.x, y1.z}, up[4] = {y0.y, y0.w, y1.y, y1.w};
             float v[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int ng = 8 * qd + 2 * e;
-                const float gt = sc(Y[ng * ldy + ml], ng, ml), up = sc(Y[(ng + 1) * ldy + ml], ng + 1, ml);
-                v[e] = gt / (1.0f + expf(-gt)) * up;
-            }
+            for (int e = 0; e < 4; ++e) v[e] = gt[e] / (1.0f + expf(-gt[e])) * up[e];
             xfrag_store4<XF32>(a, m0 + ml, (n0 >> 1) + 4 * qd, KCx, make_float4(v[0], v[1], v[2], v[3]));
         }
     }
@@ -867,15 +871,14 @@ struct EpiLM {
 
     // TPT consecutive lanes per token, each an online (max, argmax, sum exp) over a
     // slice of the rows, then a fixed shuffle tree over the slices.
-    template <class SC>
-    __device__ void operator()(float* Y, int ldy, int n0, int nrows, int m0, int mcols, int grp, char*,
-                               const SC& sc) const {
+    template <class YV, class SC>
+    __device__ void operator()(const YV& Y, int n0, int nrows, int m0, int mcols, int grp, char*, const SC& sc) const {
         if (logits != nullptr) {
             for (int idx = threadIdx.x; idx < nrows * mcols; idx += blockDim.x) {
                 const int nl = idx % nrows, ml = idx / nrows;
                 const int n = n0 + nl, m = m0 + ml;
                 if (n < V && m < M)
-                    logits[(size_t)m * V + n] = (n == mask_id) ? -INFINITY : sc(Y[nl * ldy + ml], nl, ml);
+                    logits[(size_t)m * V + n] = (n == mask_id) ? -INFINITY : sc(Y(nl, ml), nl, ml);
             }
         }
         // lanes per token: the largest power of two <= blockDim.x / mcols (groups of
@@ -890,7 +893,7 @@ struct EpiLM {
         for (int nl = b; nl < e; ++nl) {
             const int n = n0 + nl;
             if (n >= V || n == mask_id) continue;
-            const float v = sc(Y[nl * ldy + ml], nl, ml);
+            const float v = sc(Y(nl, ml), nl, ml);
             if (v > a.mx) {
                 a.s = (a.arg < 0 ? 0.f : a.s * __expf(a.mx - v)) + 1.f;
                 a.mx = v;

@@ -1,18 +1,30 @@
-// Tiled GEMM for many token rows (prompt processing): Y = X W^T with bf16 or int8
-// weights, where the streaming kernel's waves each fetch their own operand fragments
-// and the matrix cores stay ~30% busy.
+// Tiled GEMM for many token rows (prompt processing, wide windows): Y = X W^T, where the
+// streaming kernel's waves each fetch their own operand fragments and the matrix cores
+// stay ~30% busy.
 //
-// Workgroup = 8 waves = 2 row halves x 4 token quarters; it owns 16 row tiles x TT
-// token tiles (bf16: 256 rows x 256 tokens; int8: 256 x 128) and a K range (split-K
-// over grid.y, for the residual projections' partial sums).  Each K step (one weight
-// chunk: 32 columns bf16, 64 int8) its 16 weight chunks and the token tiles'
-// activation chunks (hi, lo planes; two per token tile for int8) are copied once into
-// LDS with direct global->LDS loads, three stages deep, and every wave multiplies its
-// 8 row tiles by its token tiles from there: 64 MFMAs per 16 KiB of LDS reads, against
-// 16 KiB of L1/L2 fetches per 64 MFMAs in the streaming layouts.  The packed formats
-// are the streaming kernel's (chunks are already in MFMA fragment order, so an LDS
-// chunk is read with one 16-byte load per lane; int8 is widened to bf16 after the
-// read).  Results go through the same epilogues, in four passes of TT / 4 token tiles.
+// Workgroup = 8 waves = 2 row halves x 4 token quarters; it owns RT row tiles x TT token
+// tiles and a K range (split-K over grid.y, for partial sums).  K advances in steps of 32
+// columns.  The operands are copied once per workgroup into LDS rings with direct
+// global->LDS loads: a step's activation chunks (hi and lo plane per token tile), and the
+// weights in their packed form, one chunk per row tile (32 columns bf16: one step; 64
+// columns int8 / Q4_0: two steps, so half of a chunk's tiles, or its codes and then its
+// scales, are copied per step).  Every wave multiplies its RT / 2 row tiles by its TT / 4
+// token tiles from there.  The packed formats are the streaming kernel's (chunks are
+// already in MFMA fragment order).  int8 is widened to bf16 and Q4_0 unpacked after the LDS
+// read, by each wave that uses the chunk: one widening serves TT / 2 MFMAs of 16 cycles, so
+// it hides behind the matrix cores at 16 token tiles and costs ~15% at 8.
+//
+// What bounds it: the matrix cores (two products per weight, hi and lo).  At 16 x 16 tiles a
+// step is 64 MFMAs per wave against 16 KiB of LDS reads; read at the head of the step, as
+// the scheduler arranges them, those take as long as half the MFMAs and nothing runs
+// meanwhile.  So a step's barrier stands in the middle of its products, the next step's
+// fragments are read under the second half, and each row tile's weights under the products
+// of the one before: gate/up at 4096 rows 1128 -> 1047 us (1.57 PFLOP/s of MFMAs), one
+// 16 x 16 step on an otherwise idle chip 1.26 -> 1.09 us of the 0.85 us its MFMAs take.
+// Against the streaming layouts at 473 rows Q4_0: gate/up 321 -> 212 us, QKV 169 -> 122,
+// O + down 227 -> 160; int8 at 4096 rows: gate/up 1643 -> 1285 us, O + down 981 -> 808;
+// bf16 at 200 rows: gate/up 140 -> 103 us, QKV 99 -> 73, O + down 110 -> 79.
+// Results go through the same epilogues, in four passes of TT / 4 token tiles.
 #pragma once
 
 #include "gemm.hpp"
@@ -21,62 +33,93 @@ namespace dllm {
 
 typedef __attribute__((address_space(3))) void lds_void;
 
-template <int WT>
+template <int WT, int RT_, int TT_>
 struct TiledShape {
-    static_assert(WT == WT_BF16 || WT == WT_I8, "tiled GEMM: bf16 or int8 weights");
-    static constexpr int XPER = WTraits<WT>::XPER;   // activation chunks per weight chunk
-    static constexpr int RT = 16;                    // row tiles per workgroup
-    static constexpr int WM = 4 / XPER;              // token tiles per wave
-    static constexpr int TT = 4 * WM;                // token tiles per workgroup
-    static constexpr int WR = 8;                     // row tiles per wave
-    static constexpr int S = 3;                      // LDS stages
-    static constexpr int WB = RT * 1024;             // weight bytes per stage
-    static constexpr int XB = TT * XPER * 2048;      // activation bytes per stage (hi + lo)
-    static constexpr int SB = WB + XB;
-    static constexpr int LOADS = (RT + 2 * XPER * TT) / 8;   // 1 KiB global->LDS loads per wave and stage
-    static constexpr int LDY = 16 * WM + 1;
+    static_assert(WT == WT_BF16 || WT == WT_I8 || WT == WT_Q4, "tiled GEMM: bf16, int8 or Q4_0 weights");
+    static_assert(RT_ % 2 == 0 && RT_ <= 16 && TT_ % 4 == 0 && TT_ <= 16, "at most 16 x 16 tiles");
+    static constexpr int XPER = WTraits<WT>::XPER;   // steps (activation chunks) per weight chunk
+    static constexpr int RT = RT_;                   // row tiles per workgroup
+    static constexpr int TT = TT_;                   // token tiles per workgroup
+    static constexpr int WR = RT / 2;                // row tiles per wave
+    static constexpr int WM = TT / 4;                // token tiles per wave
+    static constexpr int SX = 3;                     // activation ring slots
+    static constexpr int SW = XPER == 1 ? 4 : 3;     // weight ring slots
+    static constexpr int WCB = wchunk_bytes<WT>();   // bytes of a packed weight chunk
+    static constexpr int WB = RT * WCB + (WT == WT_Q4 ? 1024 : 0);   // weight slot (+ Q4_0 scales)
+    static constexpr int XB = TT * 2048;             // activation slot: hi + lo of every token tile
+    static constexpr int XL = TT / 4;                // 1 KiB global->LDS loads per wave and step
+    static constexpr int WL = XPER == 1 ? (RT + 7) / 8 : 1;
+    static constexpr int LOADS = XL + WL;
+    static constexpr int LDY = 16 * RT + 4;          // epilogue tile: [16 WM tokens][LDY]
+    static constexpr int RING = SW * WB + SX * XB;
+    static constexpr int YB = 16 * WM * LDY * 4;     // epilogue tile, then row scales and biases
+    static constexpr int EPI = YB + 2 * 16 * RT * 4;
+    static constexpr int SMEM = RING > EPI ? RING : EPI;
 };
 
-// m_tiles: token tiles of X (its rows / 16, a multiple of 4); rows past them are
-// never read (loads clamp to the last tile) and never written.
-template <int WT, class Epi>
+// m_tiles: token tiles of X; rows past them are never read (loads clamp to the last
+// tile) and never written.
+template <int WT, int RT_, int TT_, class Epi>
 __global__ void __launch_bounds__(512) gemm_tiled_kernel(GemmArgs g, Epi epi, int m_tiles) {
-    using T = TiledShape<WT>;
+    using T = TiledShape<WT, RT_, TT_>;
     constexpr int XPER = T::XPER;
-    static_assert(T::LOADS * 8 == T::RT + 2 * XPER * T::TT, "stage loads must split evenly over the waves");
-    static_assert(16 * T::RT * T::LDY * 4 <= T::S * T::SB, "epilogue tile must fit the stage buffers");
-    __shared__ __attribute__((aligned(1024))) char sm[T::S * T::SB];
-    constexpr int ESM = Epi::kSmem > 0 ? Epi::kSmem : 16;
-    __shared__ __align__(16) char esm[ESM];
+    __shared__ __attribute__((aligned(1024))) char sm[T::SMEM];
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wr = wave & 1, wq = wave >> 1;
     const int nt0 = blockIdx.x * T::RT, mt0 = blockIdx.z * T::TT;
     const int KC = g.KCw;
     const unsigned KS = gridDim.y;
     const int c0 = (int)((blockIdx.y * (unsigned)KC) / KS), c1 = (int)(((blockIdx.y + 1) * (unsigned)KC) / KS);
+    const int steps = (c1 - c0) * XPER;
+    char* const wring = sm;
+    char* const xring = sm + T::SW * T::WB;
 
-    // stage slot i: i < RT the weight chunk of row tile nt0 + i, else activation chunk
-    // q = i - RT: token tile q / (2 XPER), column half (q / 2) % XPER, plane q % 2;
-    // wave w copies slots w + 8j
-    auto stage = [&](int c, int buf) {
-        char* base = sm + buf * T::SB;
+    // Buffer loads: the workgroup's operands sit behind 32-bit offsets from its first tile.
+    // (With the global_load_lds form the compiler waited for every outstanding LDS read at
+    // each use of one.)
+    const char* const xsrc = (const char*)g.X + (size_t)mt0 * g.KCx * 2048;
+    const char* const wsrc = (const char*)g.W + (size_t)nt0 * KC * T::WCB;
+    [[maybe_unused]] const char* const qsrc = (const char*)g.qs + (size_t)nt0 * KC * 64;
+    auto copy16 = [&](const char* src, int voff, int soff, char* dst) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)src, 0, -1, 0x00027000),
+                                                 (lds_void*)dst, 16, voff, soff, 0, 0);
+    };
+    const int xlast = m_tiles - 1 - mt0, wlast = g.n_tiles - 1 - nt0;
+    // activation chunks of step j: 1 KiB slot q = wave + 8i is token tile q / 2, plane q % 2
+    auto stage_x = [&](int j, int slot) {
+        const int kc = c0 * XPER + min(j, steps - 1);
+        char* base = xring + slot * T::XB;
 #pragma unroll
-        for (int j = 0; j < T::LOADS; ++j) {
-            const int i = wave + 8 * j;
-            const char* src;
-            char* dst;
-            if (j < T::RT / 8) {
-                const int nt = min(nt0 + i, g.n_tiles - 1);
-                src = (const char*)g.W + (((size_t)nt * KC + c) * 64 + lane) * 16;
-                dst = base + i * 1024;
-            } else {
-                const int q = i - T::RT, tt = q / (2 * XPER), h = (q >> 1) % XPER, pl = q & 1;
-                const int mt = min(mt0 + tt, m_tiles - 1);
-                src = (const char*)g.X + ((size_t)mt * g.KCx + c * XPER + h) * 2048 + pl * 1024 + lane * 16;
-                dst = base + T::WB + q * 1024;
+        for (int i = 0; i < T::XL; ++i) {
+            const int q = wave + 8 * i;
+            copy16(xsrc, lane * 16, (min(q >> 1, xlast) * g.KCx + kc) * 2048 + (q & 1) * 1024, base + q * 1024);
+        }
+    };
+    // weight piece p.  bf16: the chunks of step p, row tiles wave, wave + 8.  int8: half
+    // p % 2 of the row tiles of chunk p / 2.  Q4_0: the codes (p even, two tiles per load)
+    // or the scales (p odd) of chunk p / 2.  A wave without a tile of its own repeats
+    // another's copy (same bytes, same place), so that every wave has the same number of
+    // loads in flight.
+    auto stage_w = [&](int p, int slot) {
+        char* base = wring + slot * T::WB;
+        const int c = c0 + min(p / XPER, c1 - c0 - 1);
+        if constexpr (XPER == 1) {
+#pragma unroll
+            for (int j = 0; j < T::WL; ++j) {
+                const int q = wave + 8 * j;
+                const int i = q < T::RT ? q : wave % T::RT;
+                copy16(wsrc, lane * 16, (min(i, wlast) * KC + c) * 1024, base + i * 1024);
             }
-            __builtin_amdgcn_global_load_lds((const void*)src, (lds_void*)dst, 16, 0, 0);
+        } else if constexpr (WT == WT_I8) {
+            const int i = (p & 1) * (T::RT / 2) + wave % (T::RT / 2);
+            copy16(wsrc, lane * 16, (min(i, wlast) * KC + c) * 1024, base + i * 1024);
+        } else if ((p & 1) == 0) {
+            const int q = wave % (T::RT / 2), i = 2 * q + (lane >> 5);
+            copy16(wsrc, min(i, wlast) * KC * 512 + (lane & 31) * 16, c * 512, base + q * 1024);
+        } else {
+            const int i = min(lane >> 2, T::RT - 1);
+            copy16(qsrc, min(i, wlast) * KC * 64 + (lane & 3) * 16, c * 64, base + T::RT * 512);
         }
     };
 
@@ -86,60 +129,155 @@ __global__ void __launch_bounds__(512) gemm_tiled_kernel(GemmArgs g, Epi epi, in
 #pragma unroll
         for (int t = 0; t < T::WM; ++t) acc[f][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    if (c1 > c0) {
-        // every step issues one stage (past the end: the last chunk again, into a
-        // buffer nobody reads), so each wave always has exactly LOADS loads of the
-        // following stage in flight when it waits for the current one
-        stage(c0, 0);
-        stage(min(c0 + 1, c1 - 1), 1);
-        for (int c = c0; c < c1; ++c) {
-            const int cur = (c - c0) % T::S;
-            // this wave's copies of stage c have landed (the next stage's may not) and
-            // its LDS reads are done; after the barrier every wave's copies have landed
-            // and nobody reads the buffer refilled next.  (__syncthreads would also wait
-            // for the next stage's copies: the fence before its barrier waits for all
-            // outstanding vector memory operations.)
-            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(T::LOADS) : "memory");
-            stage(min(c + 2, c1 - 1), (c - c0 + 2) % T::S);
-            const char* Wb = sm + cur * T::SB;
-            const char* Xb = Wb + T::WB;
-            u32x4_t xh[T::WM][XPER], xl[T::WM][XPER];
+    if (steps > 0) {
+        // Group s of loads: the activations of step s + 3 and the weights of step s + 3
+        // (64-column chunks: piece s + 4, so that a chunk's second half is in the group its
+        // first step needs); past the end, the last chunk again into a slot nobody reads.
+        // Groups -3 .. -1 go out here, group s in the middle of step s, so each wave always
+        // has exactly LOADS loads issued after the ones it waits for.
+        auto wslot = [](int p) { return (p / XPER) % T::SW; };
+        stage_w(0, 0);
+        if constexpr (XPER == 2) stage_w(1, 0);
+        stage_x(0, 0);
 #pragma unroll
-            for (int t = 0; t < T::WM; ++t)
-#pragma unroll
-                for (int h = 0; h < XPER; ++h) {
-                    const char* xp = Xb + (((T::WM * wq + t) * XPER + h) * 2) * 1024 + lane * 16;
-                    xh[t][h] = *(const u32x4_t*)xp;
-                    xl[t][h] = *(const u32x4_t*)(xp + 1024);
-                }
-#pragma unroll
-            for (int f = 0; f < T::WR; ++f) {
-                const u32x4_t raw = *(const u32x4_t*)(Wb + (T::WR * wr + f) * 1024 + lane * 16);
-                u32x4_t w[XPER];
-                if constexpr (WT == WT_I8) {
-                    w[0] = i8x8_to_bf16x8(raw[0], raw[1]);
-                    w[XPER - 1] = i8x8_to_bf16x8(raw[2], raw[3]);
+        for (int j = 1; j < 3; ++j) {
+            stage_w(j + XPER - 1, wslot(j + XPER - 1));
+            stage_x(j, j);
+        }
+        u32x4_t x[2][2 * T::WM];                   // activation fragments of a step (hi, lo) and of the next
+        [[maybe_unused]] u32x2_t held[T::WR];      // second step's half of a 64-column chunk
+        [[maybe_unused]] uint32_t hsc[T::WR];      // Q4_0: the chunk's two scales of this lane's row
+        u32x4_t raw[2];
+        const char* const xbase = xring + T::WM * wq * 2048 + lane * 16;
+        auto read_x = [&](u32x4_t* d, int t, int slot) {
+            d[2 * t] = *(const u32x4_t*)(xbase + slot * T::XB + t * 2048);
+            d[2 * t + 1] = *(const u32x4_t*)(xbase + slot * T::XB + t * 2048 + 1024);
+        };
+        // weights of row tile f (XPER 2: only at a chunk's first step h = 0)
+        auto read_w = [&](int f, int h, int slot) {
+            const char* p = wring + slot * T::WB + (T::WR * wr + f) * T::WCB;
+            if constexpr (WT == WT_BF16) {
+                raw[f & 1] = *(const u32x4_t*)(p + lane * 16);
+            } else if constexpr (WT == WT_I8) {
+                if (h == 0) raw[f & 1] = *(const u32x4_t*)(p + lane * 16);
+            } else if (h == 0) {
+                held[f] = *(const u32x2_t*)(p + lane * 8);
+                hsc[f] = *(const uint32_t*)(wring + slot * T::WB + T::RT * 512 + (T::WR * wr + f) * 64 +
+                                            (lane & 15) * 4);
+            }
+        };
+        // the products of row tile f with the wave's token tiles
+        [[maybe_unused]] f32x4_t zp[T::WM];
+        auto products = [&](int f, int h, const u32x4_t* xs) {
+            u32x4_t w;
+            if constexpr (WT == WT_Q4) {
+                w = q4_unpack(held[f][h]);
+            } else if constexpr (WT == WT_I8) {
+                if (h == 0) {
+                    w = i8x8_to_bf16x8(raw[f & 1][0], raw[f & 1][1]);
+                    held[f] = u32x2_t{raw[f & 1][2], raw[f & 1][3]};
                 } else {
-                    w[0] = raw;
+                    w = i8x8_to_bf16x8(held[f][0], held[f][1]);
                 }
+            } else {
+                w = raw[f & 1];
+            }
+            if constexpr (WT == WT_Q4) {
+                const float sc = f16_bits_to_f32(h == 0 ? (hsc[f] & 0xFFFFu) : (hsc[f] >> 16));
 #pragma unroll
-                for (int h = 0; h < XPER; ++h)
+                for (int t = 0; t < T::WM; ++t) {
+                    f32x4_t v = mfma_bf16(xs[2 * t], w, zp[t]);
+                    v = mfma_bf16(xs[2 * t + 1], w, v);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[f][t][e] = fmaf(sc, v[e], acc[f][t][e]);
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < T::WM; ++t) {
+                    acc[f][t] = mfma_bf16(w, xs[2 * t], acc[f][t]);
+                    acc[f][t] = mfma_bf16(w, xs[2 * t + 1], acc[f][t]);
+                }
+            }
+        };
+        // every scalar load is done (lgkmcnt(0), other counters untouched): the compiler
+        // does not see the waits in the asm below, and with a scalar load possibly
+        // outstanding it would wait for all LDS reads at each use instead of counting them
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * T::LOADS) : "memory");
+        int xs = 0, ws = 0;                        // ring slots of this step's activations and weights
+        int wn = wslot(XPER == 1 ? 3 : 4);         // weight slot filled next
+        auto next = [](int v, int n) { return v == n - 1 ? 0 : v + 1; };
+        read_w(0, 0, 0);
+#pragma unroll
+        for (int t = 0; t < T::WM; ++t) read_x(x[0], t, 0);
+        constexpr int F1 = T::WR / 2;              // row tiles before the step's barrier
+        constexpr int XPF = (T::WM + T::WR - F1 - 1) / (T::WR - F1);   // token tiles read per row tile after it
+        for (int i = 0; i < steps; i += 2) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (XPER == 1 && u == 1 && i + 1 >= steps) break;
+                const int h = XPER == 1 ? 0 : u;
+                const int xnext = next(xs, T::SX), wnext = (XPER == 1 || u == 1) ? next(ws, T::SW) : ws;
+                if constexpr (WT == WT_Q4) {
+                    // as in the streaming kernel: weights are the B operand, codes stand for
+                    // 128 + q, a block's products start from -136 * sum_k x
+                    const u32x4_t ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};   // bf16 1.0
 #pragma unroll
                     for (int t = 0; t < T::WM; ++t) {
-                        acc[f][t] = mfma_bf16(w[h], xh[t][h], acc[f][t]);
-                        acc[f][t] = mfma_bf16(w[h], xl[t][h], acc[f][t]);
+                        f32x4_t z = mfma_bf16(x[u][2 * t], ones, f32x4_t{0.f, 0.f, 0.f, 0.f});
+                        z = mfma_bf16(x[u][2 * t + 1], ones, z);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) zp[t][e] = -136.0f * z[e];
                     }
+                }
+#pragma unroll
+                for (int f = 0; f < T::WR; ++f) {
+                    if (f == F1) {
+                        // This wave's copies for step s + 1 have landed (group s - 1 may still be
+                        // in flight); after the barrier every wave's have, and nobody reads the
+                        // slots that group s refills: the activations of step s (already in
+                        // registers everywhere) and the weights of step s - 1.  The next
+                        // step's fragments are then read under the second half's products.
+                        // (__syncthreads would also wait for group s - 1: the fence before its
+                        // barrier waits for all outstanding vector memory operations.)
+                        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(T::LOADS) : "memory");
+                        stage_w(i + u + (XPER == 1 ? 3 : 4), wn);
+                        stage_x(i + u + 3, xs);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (f + 1 < T::WR) read_w(f + 1, h, ws);
+                    else read_w(0, XPER == 1 ? 0 : h ^ 1, wnext);
+                    if (f >= F1) {
+#pragma unroll
+                        for (int j = 0; j < XPF; ++j)
+                            if ((f - F1) * XPF + j < T::WM) read_x(x[u ^ 1], (f - F1) * XPF + j, xnext);
+                    }
+                    products(f, h, x[u]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                xs = xnext;
+                ws = wnext;
+                if (XPER == 1 || u == 1) wn = next(wn, T::SW);   // piece s + 5 starts the next chunk after an odd s
             }
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     __syncthreads();
 
-    // epilogue: four passes of WM token tiles over the stage buffers (rows 0..255 of Y)
+    // epilogue: four passes of WM token tiles over the ring buffers
     float* Y = (float*)sm;
+    float* ws_sm = (float*)(sm + T::YB);
+    float* b_sm = ws_sm + 16 * T::RT;
     const int nrows = 16 * max(0, min(T::RT, g.n_tiles - nt0));
     const int r = lane & 15, gq = lane >> 4;
-    for (int p = 0; p < T::TT / T::WM; ++p) {
+    const bool rowsc = g.wscale != nullptr || g.bias != nullptr;
+    if (rowsc) {
+        for (int n = threadIdx.x; n < nrows; n += blockDim.x) {
+            ws_sm[n] = g.wscale != nullptr ? g.wscale[nt0 * 16 + n] : 1.f;
+            b_sm[n] = g.bias != nullptr ? g.bias[nt0 * 16 + n] : 0.f;
+        }
+    }
+    for (int p = 0; p < 4; ++p) {
         const int mtp = mt0 + T::WM * p;
         if (mtp >= m_tiles || nrows == 0) break;
         const int mcols = 16 * min(T::WM, m_tiles - mtp);
@@ -147,27 +285,26 @@ __global__ void __launch_bounds__(512) gemm_tiled_kernel(GemmArgs g, Epi epi, in
 #pragma unroll
             for (int f = 0; f < T::WR; ++f)
 #pragma unroll
-                for (int t = 0; t < T::WM; ++t)
+                for (int t = 0; t < T::WM; ++t) {
+                    const int n0 = 16 * (T::WR * wr + f), m0 = 16 * t;
+                    if constexpr (WT == WT_Q4) {      // transposed: element i is token 4gq + i of row r
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        Y[(16 * (T::WR * wr + f) + 4 * gq + i) * T::LDY + 16 * t + r] = acc[f][t][i];
+                        for (int i = 0; i < 4; ++i) Y[(m0 + 4 * gq + i) * T::LDY + n0 + r] = acc[f][t][i];
+                    } else {
+                        *(f32x4_t*)(Y + (m0 + r) * T::LDY + n0 + 4 * gq) = acc[f][t];
+                    }
+                }
         }
         __syncthreads();
-        if (g.wscale != nullptr || g.bias != nullptr) {
-            for (int idx = threadIdx.x; idx < nrows * mcols; idx += blockDim.x) {
-                const int n = idx / mcols, m = idx % mcols;
-                float y = Y[n * T::LDY + m];
-                if (g.wscale != nullptr) y *= g.wscale[nt0 * 16 + n];
-                if (g.bias != nullptr) y += g.bias[nt0 * 16 + n];
-                Y[n * T::LDY + m] = y;
-            }
-            __syncthreads();
+        const YTokens<T::LDY> yv{Y};
+        if (rowsc) {
+            YScale sc;
+            if (g.wscale != nullptr) sc.ws = ws_sm;
+            if (g.bias != nullptr) sc.b = b_sm;
+            epi(yv, nt0 * 16, nrows, mtp * 16, mcols, blockIdx.x, nullptr, sc);
+        } else {
+            epi(yv, nt0 * 16, nrows, mtp * 16, mcols, blockIdx.x, nullptr, NoScale{});
         }
-        typename Epi::Pre pre;
-        epi.fetch(pre, nt0 * 16, nrows, mtp * 16, mcols);
-        epi.stage(pre, esm, nt0 * 16, nrows, mtp * 16, mcols);
-        __syncthreads();
-        epi(Y, T::LDY, nt0 * 16, nrows, mtp * 16, mcols, blockIdx.x, esm, NoScale{});
         __syncthreads();
     }
 }
@@ -180,10 +317,8 @@ __global__ void __launch_bounds__(512) gemm_tiled_kernel(GemmArgs g, Epi epi, in
 template <class Epi>
 __global__ void __launch_bounds__(256) split_epilogue_kernel(const float* P, int ks, int rows, int ldn, int n_tiles,
                                                              int m_tiles, const float* bias, Epi epi) {
-    constexpr int RT = 16, WM = 4, LDY = 16 * WM + 1;
-    __shared__ float Y[16 * RT * LDY];
-    constexpr int ESM = Epi::kSmem > 0 ? Epi::kSmem : 16;
-    __shared__ __align__(16) char esm[ESM];
+    constexpr int RT = 16, WM = 4, LDY = 16 * RT + 4;
+    __shared__ __attribute__((aligned(16))) float Y[16 * WM * LDY];
     const int nt0 = blockIdx.x * RT, mt0 = blockIdx.y * WM;
     const int nrows = 16 * min(RT, n_tiles - nt0), mcols = 16 * min(WM, m_tiles - mt0);
     const int n0 = nt0 * 16, m0 = mt0 * 16;
@@ -201,16 +336,10 @@ __global__ void __launch_bounds__(256) split_epilogue_kernel(const float* P, int
         if (bias != nullptr) {
             v.x += bias[n0 + nl]; v.y += bias[n0 + nl + 1]; v.z += bias[n0 + nl + 2]; v.w += bias[n0 + nl + 3];
         }
-        Y[nl * LDY + ml] = v.x;
-        Y[(nl + 1) * LDY + ml] = v.y;
-        Y[(nl + 2) * LDY + ml] = v.z;
-        Y[(nl + 3) * LDY + ml] = v.w;
+        *(float4*)(Y + ml * LDY + nl) = v;
     }
-    typename Epi::Pre pre;
-    epi.fetch(pre, n0, nrows, m0, mcols);
-    epi.stage(pre, esm, n0, nrows, m0, mcols);
     __syncthreads();
-    epi(Y, LDY, n0, nrows, m0, mcols, blockIdx.x, esm, NoScale{});
+    epi(YTokens<LDY>{Y}, n0, nrows, m0, mcols, blockIdx.x, nullptr, NoScale{});
 }
 
 }  // namespace dllm

@@ -1,0 +1,73 @@
+"""GPU: the LDS-tiled GEMM (every projection over more than 64 rows) at the edges of its tiles
+and K slices, against the oracle: prompts one row past a tile count, models whose row tiles
+do not fill a workgroup, an FFN width that leaves half a 64-column chunk (int8, Q4_0)."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from gpu_util import assert_logits_close, build_pair, dev_i32, gpu_logits
+
+pytestmark = pytest.mark.gpu
+
+
+def _bound(ref):
+    """K and V are rounded to fp16 once per layer (2^-11 of a value); a value that passed two
+    layers carries at most four such roundings of the largest value beside it."""
+    return 4 * 2.0 ** -11 * np.abs(ref[np.isfinite(ref)]).max()
+
+# 688 = 21.5 x 32 columns of the down projection; 43 row tiles of gate/up pairs
+RAGGED = synth.SMALL_BF16
+# grouped-query heads and biases; 1504 = 47 x 32 columns (an odd count of 32-column steps)
+GQA = dataclasses.replace(synth.SMALL_MQA, d_ff=1504)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "w8", "q4"])
+@pytest.mark.parametrize("shape,n", [(RAGGED, 65), (RAGGED, 257), (GQA, 129), (GQA, 300)],
+                         ids=["ragged65", "ragged257", "gqa129", "gqa300"])
+def test_prompt_rows_and_next_step(dtype, shape, n):
+    """The prompt's K/V in every layer and the next step's logits."""
+    import torch
+    import paper_2606_13740_amd as dl
+
+    model, om, _ = build_pair(shape, dtype, max_window=64, max_pos=n + 64)
+    kv = dl.KVCache(model, n + 64)
+    prompt = synth.prompt_ids(shape, n)
+    dl.dllm_prefill(model.handle, kv.handle, dev_i32(prompt), n)
+    torch.cuda.synchronize()
+    okv = oracle.OracleKV(shape, n + 64)
+    oracle.prefill(om, okv, prompt)
+    K, Vt = (t.cpu().numpy().astype(np.float64) for t in kv.views())
+    for l in range(shape.n_layers):
+        rk, rv = okv.K[l, :n].transpose(1, 0, 2), okv.V[l, :n].transpose(1, 0, 2)
+        assert np.abs(K[l][:, :n] - rk).max() <= _bound(rk)
+        assert np.abs(Vt[l][:, :, :n].transpose(0, 2, 1) - rv).max() <= _bound(rv)
+    tok, mask = synth.window(shape, 32, range(8, 32))
+    got, _, _ = gpu_logits(model, kv, tok, mask)
+    ref = oracle.denoise_step(om, okv, tok, mask)
+    assert_logits_close(got, ref.logits, _bound(ref.logits))
+    kv.close()
+    model.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "w8", "q4"])
+@pytest.mark.parametrize("W", [65, 96, 131, 256])
+def test_wide_window(dtype, W):
+    """Windows past 64 rows after a prompt: the tiled projections with key limits in the window."""
+    import paper_2606_13740_amd as dl
+
+    shape = RAGGED
+    model, om, _ = build_pair(shape, dtype, max_window=256, max_pos=512)
+    kv = dl.KVCache(model, 40 + W)
+    prompt = synth.prompt_ids(shape, 40)
+    dl.dllm_prefill(model.handle, kv.handle, dev_i32(prompt), 40)
+    okv = oracle.OracleKV(shape, 40 + W)
+    oracle.prefill(om, okv, prompt)
+    tok, mask = synth.window(shape, W, range(W // 3, W))
+    got, _, _ = gpu_logits(model, kv, tok, mask)
+    ref = oracle.denoise_step(om, okv, tok, mask)
+    assert_logits_close(got, ref.logits, _bound(ref.logits))
+    kv.close()
+    model.close()
