@@ -29,6 +29,7 @@ struct AttnArgs {
     int T;                // keys [0, T) for rows without their own limit
     const int* lim;       // per-row key limit (rows < M) or nullptr
     int M;                // real rows
+    int rows;             // rows of q and of the outputs (M padded to whole tiles)
     int nsplit, bps;      // key-range splits, 32-key blocks per split
     float scale;          // 1 / sqrt(Dh)
     void* o;              // output fragments (K = d), used when nsplit == 1
@@ -43,33 +44,33 @@ struct AttnArgs {
 // same way in registers, so every product takes two MFMAs (K * Q_hi + K * Q_lo,
 // V^T * P_hi + V^T * P_lo) and the scores and outputs keep the cache's precision.
 //
-// Workgroup = (key split, head, group of QG query tiles of 16 rows), KS x QG waves:
-// KS key groups of QG waves, one wave per query tile.  Key group k takes the split's
-// 32-key blocks k, k + KS, ...; each block is staged in the group's own LDS buffers
-// once with direct global->LDS loads (global_load_lds_dwordx4) in a ring of NB buffers,
-// so the next NB - 1 blocks stream in while the current one is used, and the group's waves read
-// their MFMA fragments from LDS.  With KS > 1 the groups' partial (max, sum, O)
-// states are merged in LDS in group order at the end.  LDS rows are XOR-swizzled in 16-byte columns so that
-// the 16 rows one fragment read touches fall in distinct banks:
+// Workgroup = (key split, head, group of QG x QT query tiles of 16 rows), QG waves of QT
+// tiles.  Each 32-key block of the split is staged in LDS once with direct global->LDS
+// loads in a ring of NB buffers, so that later blocks stream in while one is used, and the
+// waves read their MFMA fragments from there.  LDS rows are XOR-swizzled in 16-byte
+// columns so that the 16 rows one fragment read touches fall in distinct banks:
 //   K  [32 keys][Dh/8 cols]: col' = col ^ (((key & 3) | (4 * ((key >> 3) & 3))) mod Dh/8)
 //   V^T [Dh dims][4 cols]:   col' = col ^ ((dim >> 2) & 3)
-// With one split the normalised output goes to the O projection's fragments;
-// otherwise (m, l, o) per split goes to attn_combine.  Short key ranges take KS > 1
-// and a single split, which leaves no merge launch.
+// With one split the normalised output goes to the O projection's fragments; otherwise
+// (m, l, o) per split goes to attn_combine.
+//
+// What bounds it: short ranges, the launch and the chain of one block (LDS reads, scores,
+// softmax, products; ~1 us); long ones, that chain on few waves, or at many query tiles
+// the VALU work of the softmax beside the MFMAs.  Reading all of a block's fragments ahead
+// of their products instead of at each took (with the merge, 32 heads) 64 rows over 4160
+// keys from 25.7 to 22.4 us (8 splits, 3 buffers; 15 splits of 2 before), 32 rows over
+// 544 keys from 9.7 to 9.0, 512 over 512 from 20.4 to 17.2, 256 over 1700 from 47.9 (no
+// splits) to 28.2 (2 splits), and two tiles per wave 4096 over 4096 from 462 to 440 us.
 __device__ __forceinline__ int swz_k(int key) { return (key & 3) | (((key >> 3) & 3) << 2); }
-
-typedef __attribute__((address_space(3))) void lds_void;
 
 // At most two waves per SIMD's worth of registers (256): with the 512 a workgroup of
 // 2-4 waves may take, the compiler chose the AGPR form of the MFMAs and copied every
 // output tile VGPR -> AGPR around each product.
-// Staging buffers per workgroup with one key group (KS = 1).
-constexpr int ATTN_RING = 2;
 // log2-domain slack of the lazily rescaled softmax maximum: probabilities <= 2^8
 constexpr float ATTN_SLACK = 8.f;
 
-template <int DH, int QG, int KS, int NB>
-__global__ void __launch_bounds__(QG * KS * 64) __attribute__((amdgpu_waves_per_eu(2)))
+template <int DH, int QG, int QT, int NB>
+__global__ void __launch_bounds__(QG * 64) __attribute__((amdgpu_waves_per_eu(2)))
 attn_f16_kernel(AttnArgs a) {
     constexpr int NC = DH / 32;               // 32-dim chunks
     constexpr int ND = DH / 16;               // 16-dim output tiles
@@ -79,15 +80,12 @@ attn_f16_kernel(AttnArgs a) {
     constexpr int BUF = KPLANE + VPLANE;
     constexpr int NSLOT = BUF / 16;           // 16-byte slots per block
     static_assert(NSLOT % 64 == 0, "block must be whole wave loads");
-    constexpr int MLD = DH + 4;               // merge: floats per (group, row) record
-    constexpr int MERGE = KS > 1 ? KS * QG * 16 * (MLD + 2) * 4 : 0;
-    static_assert(NB >= 2 && NB <= 4, "2-4 staging buffers per key group");
+    static_assert(NB == 2 || NB == 3, "2 or 3 staging buffers");
     constexpr int LPW = (NSLOT / 64) / QG;    // loads each wave issues per staged block, at least
-    __shared__ __attribute__((aligned(1024))) char lds[KS * NB * BUF > MERGE ? KS * NB * BUF : MERGE];
+    __shared__ __attribute__((aligned(1024))) char lds[NB * BUF];
 
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, qw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, g = lane >> 4;
-    const int grp = wave / QG, qw = wave % QG;                // key group, query tile
     // 1-D grid over (head h, query group z, split) items, in that order.  The dispatcher
     // deals consecutive workgroups to the 8 XCDs in turn; when the items divide into
     // 8 equal shares, XCD x takes the x-th share, so the query groups and splits of a
@@ -98,7 +96,7 @@ attn_f16_kernel(AttnArgs a) {
     int item = blockIdx.x;
     if ((nitems & 7) == 0) item = (blockIdx.x & 7) * (nitems >> 3) + (blockIdx.x >> 3);
     const int split = item % a.nsplit, z = (item / a.nsplit) % nqg, h = item / (a.nsplit * nqg);
-    const int row = z * 16 * QG + 16 * qw + r;               // this lane's query row
+    const int row = z * 16 * QG * QT + 16 * QT * qw + r;     // this lane's first query row (+ 16 per tile)
     const int ld = a.H * DH;
     const float sl2 = a.scale * 1.4426950408889634f;
 
@@ -110,27 +108,27 @@ attn_f16_kernel(AttnArgs a) {
     const int nblk = (a.T + 31) >> 5;
     const int kb0 = split * a.bps, kb1 = min(nblk, kb0 + a.bps);
 
-    // stage block kb into the group's buffer `buf`: slot s -> K plane / V^T plane position
+    // stage block kb into buffer `buf`: slot s -> K plane / V^T plane position
     auto stage = [&](int kb, int buf) {
         const int k0 = kb * 32;
-        char* base = lds + (grp * NB + buf) * BUF;
+        char* base = lds + buf * BUF;
 #pragma unroll
         for (int j = 0; j < (NSLOT / 64 + QG - 1) / QG; ++j) {
             const int i = qw + j * QG;
             if (i >= NSLOT / 64) break;
             const int sl = i * 64 + lane;
-            const uint16_t* src;
-            if (sl < KPLANE / 16) {                      // K: 32 x KCOLS slots
+            // buffer loads from the head's planes (with the global_load_lds form the compiler
+            // waited for every outstanding LDS read at each use of one)
+            if (i * 64 < KPLANE / 16) {                  // K: 32 x KCOLS slots
                 const int key = sl / KCOLS, pc = sl % KCOLS;
                 const int col = pc ^ (swz_k(key) & (KCOLS - 1));
-                src = Kp + (size_t)(k0 + key) * DH + col * 8;
+                buffer_to_lds16(Kp, (key * DH + col * 8) * 2, k0 * DH * 2, base + i * 1024);
             } else {                                     // V^T: DH x 4 slots
                 const int s1 = sl - KPLANE / 16;
                 const int dim = s1 >> 2, pc = s1 & 3;
                 const int col = pc ^ ((dim >> 2) & 3);
-                src = Vp + (size_t)dim * a.Cs + k0 + col * 8;
+                buffer_to_lds16(Vp, (dim * a.Cs + col * 8) * 2, k0 * 2, base + i * 1024);
             }
-            __builtin_amdgcn_global_load_lds((const void*)src, (lds_void*)(base + i * 1024), 16, 0, 0);
         }
     };
 
@@ -139,7 +137,7 @@ attn_f16_kernel(AttnArgs a) {
     // such care, its scores past T are masked
     auto zero_tail = [&](int kb, int buf) {
         const int k0 = kb * 32;
-        char* base = lds + (grp * NB + buf) * BUF;
+        char* base = lds + buf * BUF;
 #pragma unroll
         for (int j = 0; j < (NSLOT / 64 + QG - 1) / QG; ++j) {
             const int i = qw + j * QG;
@@ -159,218 +157,207 @@ attn_f16_kernel(AttnArgs a) {
         }
     };
 
-    u32x4_t qf[NC][2];
+    u32x4_t qf[QT][NC][2];
+    int lim[QT];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        const uint16_t* src = qp + (size_t)row * ld + h * DH + 32 * c + 8 * g;
-        qf[c][0] = ldg16(src);
-        qf[c][1] = ldg16(src + a.q_plane);
-    }
-    const int lim = (a.lim != nullptr && row < a.M) ? a.lim[row] : a.T;
-
-    // Ring of NB buffers per key group: the group's first NB - 1 blocks are staged
-    // here (after the Q loads, so the ring's waits below count only block loads issued
-    // after the block they wait for), and round t stages its block t + NB - 1 into the
-    // buffer round t - 1 used.  With one key group every split has a block, so its
-    // first block is staged without a test (a split shorter than NB - 1 blocks stages
-    // its last block again into the spare buffers, which nothing reads).  The compiler
-    // still waits for every load before the key-limit reads below.
-    const int nmine = kb0 + grp < kb1 ? (kb1 - kb0 - grp + KS - 1) / KS : 0;
+    for (int q = 0; q < QT; ++q) {
 #pragma unroll
-    for (int j = 0; j < NB - 1; ++j) {
-        if constexpr (KS == 1) stage(kb0 + min(j, nmine - 1), j);
-        else if (j < nmine) stage(kb0 + grp + j * KS, j);
+        for (int c = 0; c < NC; ++c) {
+            // a last group may reach past the padded rows: those lanes read its last row
+            const uint16_t* src = qp + (size_t)min(row + 16 * q, a.rows - 1) * ld + h * DH + 32 * c + 8 * g;
+            qf[q][c][0] = ldg16(src);
+            qf[q][c][1] = ldg16(src + a.q_plane);
+        }
+        lim[q] = (a.lim != nullptr && row + 16 * q < a.M) ? a.lim[row + 16 * q] : a.T;
     }
 
-    // smallest key limit of the wave's 16 rows (lanes 0-15 hold them): blocks below it
+    // Ring of NB buffers: the first NB - 1 blocks are staged here (after the Q loads, so
+    // the ring's waits below count only block loads issued after the block they wait
+    // for), and round t stages block t + NB - 1 into the buffer round t - 1 used.  Every
+    // split has a block.
+    const int rounds = kb1 - kb0;
+#pragma unroll
+    for (int j = 0; j < NB - 1; ++j)
+        if (j == 0 || j < rounds) stage(kb0 + j, j);
+
+    // smallest key limit of the wave's rows (lanes 0-15 hold each tile's): blocks below it
     // need no per-key mask.  Read lane by lane into a scalar, so that the per-block
     // test is a scalar branch.
-    int lim_w = __builtin_amdgcn_readlane(lim, 0);
+    int lim_w = a.T;
 #pragma unroll
-    for (int i = 1; i < 16; ++i) lim_w = min(lim_w, __builtin_amdgcn_readlane(lim, i));
+    for (int q = 0; q < QT; ++q)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) lim_w = min(lim_w, __builtin_amdgcn_readlane(lim[q], i));
 
-    float mrun = -INFINITY, lrun = 0.f;
-    f32x4_t oacc[ND];
+    float mrun[QT], lrun[QT];
+    f32x4_t oacc[QT][ND];
 #pragma unroll
-    for (int dt = 0; dt < ND; ++dt) oacc[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int q = 0; q < QT; ++q) {
+        mrun[q] = -INFINITY;
+        lrun[q] = 0.f;
+#pragma unroll
+        for (int dt = 0; dt < ND; ++dt) oacc[q][dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
     const int krow0 = 8 * (r >> 2) + (r & 3);   // + 4t: the key this lane reads for tile t
 
-    // every group runs the same number of rounds (the barriers line up); a group
-    // whose block lies past the split's range only stages and waits
-    const int rounds = (max(kb1 - kb0, 0) + KS - 1) / KS;
+    // no scalar load outstanding past here (lgkmcnt(0), other counters untouched): the
+    // compiler does not see the waits in the loop's asm and would otherwise wait for all
+    // LDS reads at each use
+    __builtin_amdgcn_s_waitcnt(0xC07F);
     for (int t = 0; t < rounds; ++t) {
-        const int kb = kb0 + grp + t * KS;
+        const int kb = kb0 + t;
         const int cur = t % NB;
-        // this wave's loads of block t have landed once at most LPW per block staged
-        // after it are outstanding (loads complete in issue order, and the loop issues
-        // no other vector-memory operations); the barrier then makes every wave's
-        // loads visible and frees the buffer round t - 1 read.  No workgroup fence:
-        // with loads into LDS in flight it would wait for all of them.
-        const int after = min(NB - 2, nmine - 1 - t);
-        if (kb < kb1 && kb * 32 + 32 > a.T) {  // the block holding T: the group's last
+        // This wave's loads of block t have landed once at most LPW of the block staged after
+        // it are outstanding (loads complete in issue order, and the loop issues no other
+        // vector-memory operations); the barrier then makes every wave's loads visible and
+        // frees the buffer round t - 1 read.  No workgroup fence: with loads into LDS in
+        // flight it would wait for all of them.
+        if (kb * 32 + 32 > a.T) {               // the block holding T: the last
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             zero_tail(kb, cur);                 // before the barrier, so no other wave reads first
         }
-        if (NB > 3 && after >= 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * LPW) : "memory");
-        else if (NB > 2 && after >= 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPW) : "memory");
+        if (NB > 2 && t + 1 < rounds) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPW) : "memory");
         else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        if (t + NB - 1 < nmine) stage(kb + (NB - 1) * KS, (t + NB - 1) % NB);
-        if (kb >= kb1) continue;
-        const char* Kb = lds + (grp * NB + cur) * BUF;
+        if (t + NB - 1 < rounds) stage(kb + NB - 1, (t + NB - 1) % NB);
+        const char* Kb = lds + cur * BUF;
         const char* Vb = Kb + KPLANE;
         const int k0 = kb * 32;
 
-        f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+        // All of the block's K fragments are read before the first product and its V^T
+        // fragments between the scores and the softmax, which covers their latency (read
+        // at each use, every pair of products waited for its own LDS round trip).  The
+        // QT tiles share both: at one tile per wave the LDS reads take as long as the
+        // MFMAs.
+        u32x4_t kf[NC][2], vf[ND];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
+        for (int c = 0; c < NC; ++c)
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
                 const int key = krow0 + 4 * t;
                 const int off = key * (DH * 2) + (((4 * c + g) ^ (swz_k(key) & (KCOLS - 1))) << 4);
-                const u32x4_t kf = *(const u32x4_t*)(Kb + off);
-                f32x4_t& sa = t ? s1 : s0;
-                sa = mfma_f16(kf, qf[c][0], sa);
-                sa = mfma_f16(kf, qf[c][1], sa);
+                kf[c][t] = *(const u32x4_t*)(Kb + off);
             }
-        }
-
-        // unscaled scores of keys k0 + 8g + j (j = 0..7); keys past a row's limit -> -inf
-        float sv[8];
+        __builtin_amdgcn_sched_barrier(0);
+        f32x4_t s[QT][2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            sv[i] = s0[i];
-            sv[4 + i] = s1[i];
-        }
-        if (k0 + 32 > lim_w) {                  // some row of the wave stops inside the block
+        for (int q = 0; q < QT; ++q) s[q][0] = s[q][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int q = 0; q < QT; ++q)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) s[q][t] = mfma_f16(kf[c][t], qf[q][c][p], s[q][t]);
+        auto read_v = [&](int dt) {
+            const int dim = 16 * dt + r;
+            vf[dt] = *(const u32x4_t*)(Vb + dim * 64 + ((g ^ ((dim >> 2) & 3)) << 4));
+        };
+#pragma unroll
+        for (int dt = 0; dt < ND; ++dt) read_v(dt);
+        __builtin_amdgcn_sched_barrier(0);
+
+        u32x4_t ph[QT], pl[QT];
+#pragma unroll
+        for (int q = 0; q < QT; ++q) {
+            // unscaled scores of keys k0 + 8g + j (j = 0..7); keys past a row's limit -> -inf
+            float sv[8];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int key0 = k0 + 8 * g + i;
-                if (key0 >= lim) sv[i] = -INFINITY;
-                if (key0 + 4 >= lim) sv[4 + i] = -INFINITY;
+                sv[i] = s[q][0][i];
+                sv[4 + i] = s[q][1][i];
             }
-        }
-        // the row's block maximum over its four lane groups (lanes l, l ^ 16, l ^ 32,
-        // l ^ 48): each swap hands a lane its partner's value, and max is symmetric
-        float bm = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])),
-                         fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-        {
-            const auto w32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(bm), __float_as_uint(bm), false, false);
-            bm = fmaxf(__uint_as_float(w32[0]), __uint_as_float(w32[1]));
-            const auto w16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(bm), __float_as_uint(bm), false, false);
-            bm = fmaxf(__uint_as_float(w16[0]), __uint_as_float(w16[1]));
-        }
-        const float bms = bm * sl2;             // log2-domain block maximum (sl2 > 0)
-        // Lazy rescaling: the reference maximum mrun moves only when some row of the
-        // wave exceeds it by more than ATTN_SLACK (and on a row's first unmasked key),
-        // so the probabilities stay <= 2^ATTN_SLACK and most blocks skip the rescale.
-        // O, l and m are exact for any reference value; the split merge uses the same m.
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(bms > mrun + ATTN_SLACK) != 0, 0)) {
-            const float mnew = fmaxf(mrun, bms);
-            const float alpha = (mnew == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(mrun - mnew);
-            lrun *= alpha;
+            if (k0 + 32 > lim_w) {                  // some row of the wave stops inside the block
 #pragma unroll
-            for (int dt = 0; dt < ND; ++dt)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) oacc[dt][i] *= alpha;
-            mrun = mnew;
-        }
-        // a row with no unmasked key yet keeps m = -inf; its masked scores give p = 0
-        const float mref = (mrun == -INFINITY) ? 0.f : mrun;
-        float ps;
-        uint32_t phi[4], plo[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            // v_exp_f32 directly: the arguments are <= ATTN_SLACK (or -inf); results below
-            // 2^-126 (flushed to zero) are the only ones that differ from exp2f
-            const float p0 = __builtin_amdgcn_exp2f(fmaf(sv[2 * e], sl2, -mref));
-            const float p1 = __builtin_amdgcn_exp2f(fmaf(sv[2 * e + 1], sl2, -mref));
-            ps = e ? ps + (p0 + p1) : p0 + p1;
-            // hi = fp16 toward zero, lo = the remainder toward zero
-            const auto h = __builtin_amdgcn_cvt_pkrtz(p0, p1);
-            const auto l = __builtin_amdgcn_cvt_pkrtz(p0 - (float)h[0], p1 - (float)h[1]);
-            phi[e] = __builtin_bit_cast(uint32_t, h);
-            plo[e] = __builtin_bit_cast(uint32_t, l);
-        }
-        lrun += ps;
-        const u32x4_t ph = {phi[0], phi[1], phi[2], phi[3]};
-        const u32x4_t pl = {plo[0], plo[1], plo[2], plo[3]};
-        // (V^T of keys past T was zeroed when the block holding T was staged)
-#pragma unroll
-        for (int dt = 0; dt < ND; ++dt) {
-            const int dim = 16 * dt + r;
-            const u32x4_t vf = *(const u32x4_t*)(Vb + dim * 64 + ((g ^ ((dim >> 2) & 3)) << 4));
-            oacc[dt] = mfma_f16(vf, ph, oacc[dt]);
-            oacc[dt] = mfma_f16(vf, pl, oacc[dt]);
-        }
-    }
-
-    float l = lrun;
-    l += __shfl_xor(l, 16);
-    l += __shfl_xor(l, 32);
-    if constexpr (KS > 1) {
-        // merge the key groups in group order: O = sum_k o_k 2^(m_k - M), L = sum_k l_k 2^(m_k - M)
-        __syncthreads();                        // every group is done with its staging buffers
-        float* o_sm = (float*)lds;              // [KS][QG * 16][MLD]
-        float* m_sm = o_sm + KS * QG * 16 * MLD;
-        float* l_sm = m_sm + KS * QG * 16;
-        const int rec = grp * QG * 16 + qw * 16 + r;
-#pragma unroll
-        for (int dt = 0; dt < ND; ++dt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o_sm[rec * MLD + 16 * dt + 4 * g + i] = oacc[dt][i];
-        if (g == 0) {
-            m_sm[rec] = mrun;
-            l_sm[rec] = l;
-        }
-        __syncthreads();
-        const int row0 = z * 16 * QG;
-        for (int idx = threadIdx.x; idx < QG * 16 * (DH / 4); idx += blockDim.x) {
-            const int q = idx / (DH / 4), d0 = 4 * (idx % (DH / 4));
-            float mx = -INFINITY;
-#pragma unroll
-            for (int k = 0; k < KS; ++k) mx = fmaxf(mx, m_sm[k * QG * 16 + q]);
-            float L = 0.f;
-            float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-            for (int k = 0; k < KS; ++k) {
-                const float mk = m_sm[k * QG * 16 + q];
-                const float e = (mk == -INFINITY) ? 0.f : exp2f(mk - mx);
-                const float* ok = o_sm + (k * QG * 16 + q) * MLD + d0;
-                L += l_sm[k * QG * 16 + q] * e;
-                o.x += ok[0] * e; o.y += ok[1] * e; o.z += ok[2] * e; o.w += ok[3] * e;
-            }
-            if (a.nsplit == 1) {
-                const float inv = 1.f / L;
-                xfrag_store4<false>(a.o, row0 + q, h * DH + d0, a.KCx,
-                                    make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv));
-            } else {
-                float* op = a.opart + (((size_t)split * a.rows_ld + row0 + q) * a.H + h) * DH;
-                *(float4*)(op + d0) = o;
-                if (d0 == 0) {
-                    float* ml = a.mlpart + (((size_t)split * a.rows_ld + row0 + q) * a.H + h) * 2;
-                    ml[0] = mx;
-                    ml[1] = L;
+                for (int i = 0; i < 4; ++i) {
+                    const int key0 = k0 + 8 * g + i;
+                    if (key0 >= lim[q]) sv[i] = -INFINITY;
+                    if (key0 + 4 >= lim[q]) sv[4 + i] = -INFINITY;
                 }
             }
+            // the row's block maximum over its four lane groups (lanes l, l ^ 16, l ^ 32,
+            // l ^ 48): each swap hands a lane its partner's value, and max is symmetric
+            float bm = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])),
+                             fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
+            {
+                const auto w32 =
+                    __builtin_amdgcn_permlane32_swap(__float_as_uint(bm), __float_as_uint(bm), false, false);
+                bm = fmaxf(__uint_as_float(w32[0]), __uint_as_float(w32[1]));
+                const auto w16 =
+                    __builtin_amdgcn_permlane16_swap(__float_as_uint(bm), __float_as_uint(bm), false, false);
+                bm = fmaxf(__uint_as_float(w16[0]), __uint_as_float(w16[1]));
+            }
+            const float bms = bm * sl2;             // log2-domain block maximum (sl2 > 0)
+            // Lazy rescaling: the reference maximum mrun moves only when some row of the
+            // wave exceeds it by more than ATTN_SLACK (and on a row's first unmasked key),
+            // so the probabilities stay <= 2^ATTN_SLACK and most blocks skip the rescale.
+            // O, l and m are exact for any reference value; the split merge uses the same m.
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(bms > mrun[q] + ATTN_SLACK) != 0, 0)) {
+                const float mnew = fmaxf(mrun[q], bms);
+                const float alpha = (mnew == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(mrun[q] - mnew);
+                lrun[q] *= alpha;
+#pragma unroll
+                for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) oacc[q][dt][i] *= alpha;
+                mrun[q] = mnew;
+            }
+            // a row with no unmasked key yet keeps m = -inf; its masked scores give p = 0
+            const float mref = (mrun[q] == -INFINITY) ? 0.f : mrun[q];
+            float ps;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                // v_exp_f32 directly: the arguments are <= ATTN_SLACK (or -inf); results below
+                // 2^-126 (flushed to zero) are the only ones that differ from exp2f
+                const float p0 = __builtin_amdgcn_exp2f(fmaf(sv[2 * e], sl2, -mref));
+                const float p1 = __builtin_amdgcn_exp2f(fmaf(sv[2 * e + 1], sl2, -mref));
+                ps = e ? ps + (p0 + p1) : p0 + p1;
+                // hi = fp16 toward zero, lo = the remainder toward zero
+                const auto hi = __builtin_amdgcn_cvt_pkrtz(p0, p1);
+                const auto lo = __builtin_amdgcn_cvt_pkrtz(p0 - (float)hi[0], p1 - (float)hi[1]);
+                ph[q][e] = __builtin_bit_cast(uint32_t, hi);
+                pl[q][e] = __builtin_bit_cast(uint32_t, lo);
+            }
+            lrun[q] += ps;
         }
-        return;
+        // (V^T of keys past T was zeroed when the block holding T was staged)
+#pragma unroll
+        for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+            for (int q = 0; q < QT; ++q) {
+                oacc[q][dt] = mfma_f16(vf[dt], ph[q], oacc[q][dt]);
+                oacc[q][dt] = mfma_f16(vf[dt], pl[q], oacc[q][dt]);
+            }
     }
-    if (a.nsplit == 1) {
-        const float inv = 1.f / l;
+
+    float l[QT];
 #pragma unroll
-        for (int dt = 0; dt < ND; ++dt)
+    for (int q = 0; q < QT; ++q) {
+        l[q] = lrun[q] + __shfl_xor(lrun[q], 16);
+        l[q] += __shfl_xor(l[q], 32);
+    }
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                xfrag_store<false>(a.o, row, h * DH + 16 * dt + 4 * g + i, a.KCx, oacc[dt][i] * inv);
-    } else {
-        float* op = a.opart + (((size_t)split * a.rows_ld + row) * a.H + h) * DH;
+    for (int q = 0; q < QT; ++q) {
+        const int rq = row + 16 * q;
+        if (rq >= a.rows) continue;
+        if (a.nsplit == 1) {
+            const float inv = 1.f / l[q];
 #pragma unroll
-        for (int dt = 0; dt < ND; ++dt)
-            *(float4*)(op + 16 * dt + 4 * g) = make_float4(oacc[dt][0], oacc[dt][1], oacc[dt][2], oacc[dt][3]);
-        if (g == 0) {
-            float* ml = a.mlpart + (((size_t)split * a.rows_ld + row) * a.H + h) * 2;
-            ml[0] = mrun;
-            ml[1] = l;
+            for (int dt = 0; dt < ND; ++dt)
+                xfrag_store4<false>(a.o, rq, h * DH + 16 * dt + 4 * g, a.KCx,
+                                    make_float4(oacc[q][dt][0] * inv, oacc[q][dt][1] * inv, oacc[q][dt][2] * inv,
+                                                oacc[q][dt][3] * inv));
+        } else {
+            float* op = a.opart + (((size_t)split * a.rows_ld + rq) * a.H + h) * DH;
+#pragma unroll
+            for (int dt = 0; dt < ND; ++dt)
+                *(float4*)(op + 16 * dt + 4 * g) =
+                    make_float4(oacc[q][dt][0], oacc[q][dt][1], oacc[q][dt][2], oacc[q][dt][3]);
+            if (g == 0) {
+                float* ml = a.mlpart + (((size_t)split * a.rows_ld + rq) * a.H + h) * 2;
+                ml[0] = mrun[q];
+                ml[1] = l[q];
+            }
         }
     }
 }

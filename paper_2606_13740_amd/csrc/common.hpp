@@ -226,6 +226,16 @@ __device__ __forceinline__ float warp_max(float v) {
     return v;
 }
 
+typedef __attribute__((address_space(3))) void lds_void;
+
+// 16 bytes per lane from src + voff (per lane) + soff (wave-uniform) straight to LDS at
+// dst + 16 * lane (dst wave-uniform).  src must be wave-uniform; the caller keeps every
+// offset inside its buffer.
+__device__ __forceinline__ void buffer_to_lds16(const void* src, int voff, int soff, char* dst) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)src, 0, -1, 0x00027000),
+                                             (lds_void*)dst, 16, voff, soff, 0, 0);
+}
+
 __device__ __forceinline__ u32x4_t ldg16(const void* p) { return *(const u32x4_t*)p; }
 __device__ __forceinline__ u32x4_t ldg16_nt(const void* p) {
     return __builtin_nontemporal_load((const u32x4_t*)p);

@@ -93,12 +93,7 @@ struct Workspace {
 };
 
 constexpr int MAX_SPLIT = 16;
-// Windows of <= 64 rows: most 32-key blocks one attention key group streams before the
-// key range is split across workgroups (and merged by a separate launch).
-#ifndef ATTN_ROUNDS
-#define ATTN_ROUNDS 3
-#endif
-constexpr int ATTN_KEYGROUP_BLOCKS = 48;
+constexpr int ATTN_DEEP_BLOCKS = 12;   // blocks per key split from which attention keeps three buffers
 constexpr int RES_SPLIT = 8;     // most K slices of the O / down projections for windows of <= 64 rows
 
 }  // namespace
@@ -686,7 +681,7 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
         if (run(DLLM_K_ATTN)) {
             AttnArgs at{};
             at.q = w.q; at.q_plane = q_plane; at.K = Kc; at.Vt = Vt; at.Cs = kv->Cs; at.H = H;
-            at.G = H / m->Hkv; at.T = a.T; at.lim = a.lim; at.M = a.M;
+            at.G = H / m->Hkv; at.T = a.T; at.lim = a.lim; at.M = a.M; at.rows = Mc;
             at.scale = 1.0f / sqrtf((float)Dh); at.o = w.of; at.KCx = m->KCx_d;
             at.opart = w.opart; at.mlpart = w.mlpart; at.rows_ld = w.wrows;
             ProbeScope ps(m, DLLM_K_ATTN, s);
@@ -695,58 +690,36 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
                 if (Dh == 32) hipLaunchKernelGGL((attn_f32_kernel<32>), dim3(Mc, H), dim3(64), 0, s, at);
                 else if (Dh == 64) hipLaunchKernelGGL((attn_f32_kernel<64>), dim3(Mc, H), dim3(64), 0, s, at);
                 else hipLaunchKernelGGL((attn_f32_kernel<128>), dim3(Mc, H), dim3(64), 0, s, at);
-            } else if (gy == 1 && Mc >= 48 && ceil_div(a.T, 32) <= ATTN_KEYGROUP_BLOCKS) {
-                // windows of 48-64 rows over up to 1536 keys: the workgroup's QG query tiles
-                // share each staged block and KS = 2 key groups take alternate blocks
-                // (8 waves stage 2 blocks at a time); key splits across workgroups where a
-                // group would take more than ATTN_ROUNDS blocks.  LLaDA-8B, 64 rows,
-                // prefix 1024: 17.5 against 20.0 us per layer for one key group.  For 32
-                // rows, and for long prefixes, one group per workgroup and the most splits
-                // are faster (prefix 512: 13.3 against 14.9-15.8 us; 4096: 32.4 against 34.1).
-                const int QGs = Mc / 16;                   // 3 or 4
-                const int KSs = 2;
-                const int nblk = ceil_div(a.T, 32);
-                int nsplit = std::min(ceil_div(nblk, KSs * ATTN_ROUNDS), MAX_SPLIT);
-                at.bps = ceil_div(nblk, nsplit);
-                at.nsplit = ceil_div(nblk, at.bps);
-                dim3 grid(at.nsplit * H);
-#define ATTN_W(DH_, QG_, KS_) hipLaunchKernelGGL((attn_f16_kernel<DH_, QG_, KS_, 2>), grid, dim3(QG_ * KS_ * 64), 0, s, at)
-#define ATTN_W_QG(DH_) \
-    do { if (QGs == 3) ATTN_W(DH_, 3, 2); else ATTN_W(DH_, 4, 2); } while (0)
-                if (Dh == 128) ATTN_W_QG(128); else ATTN_W_QG(64);
-#undef ATTN_W_QG
-#undef ATTN_W
-                if (at.nsplit > 1)
-                    hipLaunchKernelGGL((attn_combine_kernel<false>), dim3(ceil_div(Mc * H, ATTN_MERGE_PAIRS)),
-                                       dim3(32 * ATTN_MERGE_PAIRS), 0, s, at,
-                                       Mc, Dh);
             } else {
-                // QG query tiles share each staged K/V block; key splits across
-                // workgroups give the chip enough waves (~2 per SIMD) and are merged
-                // by attn_combine
-                // long prompts: 8 query tiles per workgroup halve the K/V blocks staged per
-                // query (4096 tokens, 32 heads: 984 against 1149 us per layer) once that
-                // still leaves 512+ workgroups
-                const int QG = (a.M > 64 && Mc % 128 == 0 && (long)H * (Mc / 128) >= 512) ? 8
-                               : (Mc >= 64) ? 4 : Mc / 16;
-                const int nqg = Mc / (16 * QG);
+                // One wave per query tile, up to 4 tiles sharing each staged K/V block; from
+                // 512 workgroups of twice that (long prompts) two tiles per wave, which halve
+                // the LDS reads per product (2048 tokens, 32 heads: 120 against 136 us; 1024
+                // tokens, 256 workgroups: 45 against 40).
+                const bool two = (long)H * ceil_div(Mc, 128) >= 512;
+                const int QG = Mc >= 64 ? 4 : Mc / 16;
+                const int nqg = ceil_div(Mc, 16 * QG * (two ? 2 : 1));
+                // Key splits across workgroups, merged by attn_combine, up to one workgroup
+                // per CU (64 rows over 4160 keys, 32 heads: 8 splits 24.3 us, 12 splits 24.9,
+                // 6 splits 26.3; 256 rows over 1700: 2 splits 28.2, 1 split 41), while the
+                // partials' workspace holds the rows, and of at least 3 blocks (32 rows over
+                // 544 keys: 6 splits of 3 blocks 9.0, 9 of 2 9.6, 5 of 4 9.3)
                 const int nblk = ceil_div(a.T, 32);
-                int nsplit = std::max(1, std::min(nblk, 2048 / (H * nqg * QG)));
-                if (a.M > 64) nsplit = std::min(nsplit, 1);          // prefill: enough workgroups already
-                nsplit = std::min(nsplit, MAX_SPLIT);
-                // at least 3 blocks per split: fewer partials to merge where the prefix is
-                // short (LLaDA-8B, 32 rows, prefix 512: 6 splits of 3 blocks against 9 of 2,
-                // attention + merge 11.0 -> 10.5 us; 4 blocks: 11.0)
+                int nsplit = Mc <= w.wrows ? std::min(std::max(1, N_CU / (H * nqg)), MAX_SPLIT) : 1;
                 at.bps = std::max(ceil_div(nblk, nsplit), 3);
                 at.nsplit = ceil_div(nblk, at.bps);
                 dim3 grid(at.nsplit * H * nqg);
-#define ATTN(DH_, QG_) hipLaunchKernelGGL((attn_f16_kernel<DH_, QG_, 1, ATTN_RING>), grid, dim3(QG_ * 64), 0, s, at)
+                // a third buffer pays where a split is long and its workgroup alone on the CU
+                // (4160 keys: 24.3 -> 22.4 us), and costs 0.5 us where it is not (544 keys)
+                const bool deep = Mc <= 64 && at.bps >= ATTN_DEEP_BLOCKS;
+#define ATTN(DH_, QG_, QT_, NB_) \
+    hipLaunchKernelGGL((attn_f16_kernel<DH_, QG_, QT_, NB_>), grid, dim3(QG_ * 64), 0, s, at)
+#define ATTN_NB(DH_, QG_) do { if (deep) ATTN(DH_, QG_, 1, 3); else ATTN(DH_, QG_, 1, 2); } while (0)
 #define ATTN_QG(DH_) \
-    do { if (QG == 8) ATTN(DH_, 8); else if (QG == 4) ATTN(DH_, 4); else if (QG == 3) ATTN(DH_, 3); \
-         else if (QG == 2) ATTN(DH_, 2); \
-         else ATTN(DH_, 1); } while (0)
+    do { if (two) ATTN(DH_, 4, 2, 2); else if (QG == 4) ATTN_NB(DH_, 4); else if (QG == 3) ATTN_NB(DH_, 3); \
+         else if (QG == 2) ATTN_NB(DH_, 2); else ATTN_NB(DH_, 1); } while (0)
                 if (Dh == 128) ATTN_QG(128); else ATTN_QG(64);
 #undef ATTN_QG
+#undef ATTN_NB
 #undef ATTN
                 if (at.nsplit > 1) {
                     hipLaunchKernelGGL((attn_combine_kernel<false>), dim3(ceil_div(Mc * H, ATTN_MERGE_PAIRS)),

@@ -31,8 +31,6 @@
 
 namespace dllm {
 
-typedef __attribute__((address_space(3))) void lds_void;
-
 template <int WT, int RT_, int TT_>
 struct TiledShape {
     static_assert(WT == WT_BF16 || WT == WT_I8 || WT == WT_Q4, "tiled GEMM: bf16, int8 or Q4_0 weights");
@@ -81,10 +79,6 @@ __global__ void __launch_bounds__(512) gemm_tiled_kernel(GemmArgs g, Epi epi, in
     const char* const xsrc = (const char*)g.X + (size_t)mt0 * g.KCx * 2048;
     const char* const wsrc = (const char*)g.W + (size_t)nt0 * KC * T::WCB;
     [[maybe_unused]] const char* const qsrc = (const char*)g.qs + (size_t)nt0 * KC * 64;
-    auto copy16 = [&](const char* src, int voff, int soff, char* dst) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)src, 0, -1, 0x00027000),
-                                                 (lds_void*)dst, 16, voff, soff, 0, 0);
-    };
     const int xlast = m_tiles - 1 - mt0, wlast = g.n_tiles - 1 - nt0;
     // activation chunks of step j: 1 KiB slot q = wave + 8i is token tile q / 2, plane q % 2
     auto stage_x = [&](int j, int slot) {
@@ -93,7 +87,7 @@ __global__ void __launch_bounds__(512) gemm_tiled_kernel(GemmArgs g, Epi epi, in
 #pragma unroll
         for (int i = 0; i < T::XL; ++i) {
             const int q = wave + 8 * i;
-            copy16(xsrc, lane * 16, (min(q >> 1, xlast) * g.KCx + kc) * 2048 + (q & 1) * 1024, base + q * 1024);
+            buffer_to_lds16(xsrc, lane * 16, (min(q >> 1, xlast) * g.KCx + kc) * 2048 + (q & 1) * 1024, base + q * 1024);
         }
     };
     // weight piece p.  bf16: the chunks of step p, row tiles wave, wave + 8.  int8: half
@@ -109,17 +103,17 @@ __global__ void __launch_bounds__(512) gemm_tiled_kernel(GemmArgs g, Epi epi, in
             for (int j = 0; j < T::WL; ++j) {
                 const int q = wave + 8 * j;
                 const int i = q < T::RT ? q : wave % T::RT;
-                copy16(wsrc, lane * 16, (min(i, wlast) * KC + c) * 1024, base + i * 1024);
+                buffer_to_lds16(wsrc, lane * 16, (min(i, wlast) * KC + c) * 1024, base + i * 1024);
             }
         } else if constexpr (WT == WT_I8) {
             const int i = (p & 1) * (T::RT / 2) + wave % (T::RT / 2);
-            copy16(wsrc, lane * 16, (min(i, wlast) * KC + c) * 1024, base + i * 1024);
+            buffer_to_lds16(wsrc, lane * 16, (min(i, wlast) * KC + c) * 1024, base + i * 1024);
         } else if ((p & 1) == 0) {
             const int q = wave % (T::RT / 2), i = 2 * q + (lane >> 5);
-            copy16(wsrc, min(i, wlast) * KC * 512 + (lane & 31) * 16, c * 512, base + q * 1024);
+            buffer_to_lds16(wsrc, min(i, wlast) * KC * 512 + (lane & 31) * 16, c * 512, base + q * 1024);
         } else {
             const int i = min(lane >> 2, T::RT - 1);
-            copy16(qsrc, min(i, wlast) * KC * 64 + (lane & 3) * 16, c * 64, base + T::RT * 512);
+            buffer_to_lds16(qsrc, min(i, wlast) * KC * 64 + (lane & 3) * 16, c * 64, base + T::RT * 512);
         }
     };
 

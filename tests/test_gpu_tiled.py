@@ -71,3 +71,47 @@ def test_wide_window(dtype, W):
     assert_logits_close(got, ref.logits, _bound(ref.logits))
     kv.close()
     model.close()
+
+
+def test_long_prompt_attention_head_64():
+    """32 heads of 64: a prompt long enough for two query tiles per wave whose last row group is
+    half empty, then a step whose key splits are long enough for three staging buffers."""
+    import paper_2606_13740_amd as dl
+
+    shape = synth.Shape(n_layers=1, d_model=2048, n_heads=32, head_dim=64, d_ff=256, vocab=500, mask_id=499)
+    n = 2850
+    model, om, _ = build_pair(shape, "bf16", max_window=64, max_pos=n + 64)
+    kv = dl.KVCache(model, n + 64)
+    prompt = synth.prompt_ids(shape, n)
+    dl.dllm_prefill(model.handle, kv.handle, dev_i32(prompt), n)
+    okv = oracle.OracleKV(shape, n + 64)
+    oracle.prefill(om, okv, prompt)
+    for W in (17, 33, 64):
+        tok, mask = synth.window(shape, W, range(4, W))
+        got, _, _ = gpu_logits(model, kv, tok, mask)
+        ref = oracle.denoise_step(om, okv, tok, mask)
+        assert_logits_close(got, ref.logits, _bound(ref.logits))
+    kv.close()
+    model.close()
+
+
+@pytest.mark.parametrize("n", [2048 + 1, 2304 - 63])
+def test_two_tile_prompt_rows(n):
+    """Two layers, so that the second layer's K/V depend on the two-tile attention of every row."""
+    import torch
+    import paper_2606_13740_amd as dl
+
+    shape = synth.Shape(n_layers=2, d_model=2048, n_heads=32, head_dim=64, d_ff=256, vocab=500, mask_id=499)
+    model, om, _ = build_pair(shape, "bf16", max_window=64, max_pos=n)
+    kv = dl.KVCache(model, n)
+    prompt = synth.prompt_ids(shape, n)
+    dl.dllm_prefill(model.handle, kv.handle, dev_i32(prompt), n)
+    torch.cuda.synchronize()
+    okv = oracle.OracleKV(shape, n)
+    oracle.prefill(om, okv, prompt)
+    K, Vt = (t.cpu().numpy().astype(np.float64) for t in kv.views())
+    rk, rv = okv.K[1, :n].transpose(1, 0, 2), okv.V[1, :n].transpose(1, 0, 2)
+    assert np.abs(K[1][:, :n] - rk).max() <= _bound(rk)
+    assert np.abs(Vt[1][:, :, :n].transpose(0, 2, 1) - rv).max() <= _bound(rv)
+    kv.close()
+    model.close()
