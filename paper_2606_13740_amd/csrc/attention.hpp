@@ -78,13 +78,13 @@ attn_f16_kernel(AttnArgs a) {
     constexpr int KPLANE = 32 * DH * 2;       // bytes of a block's K (fp16)
     constexpr int VPLANE = DH * 64;           // bytes of a block's V^T (fp16)
     constexpr int BUF = KPLANE + VPLANE;
-    constexpr int NSLOT = BUF / 16;           // 16-byte slots per block
-    static_assert(NSLOT % 64 == 0, "block must be whole wave loads");
+    constexpr int KI = KPLANE / 1024, VI = VPLANE / 1024;   // 1 KiB wave loads per block
+    static_assert(KI * 1024 == KPLANE && VI * 1024 == VPLANE, "planes must be whole wave loads");
     static_assert(NB == 2 || NB == 3, "2 or 3 staging buffers");
-    constexpr int LPW = (NSLOT / 64) / QG;    // loads each wave issues per staged block, at least
+    constexpr int LPW = KI / QG + VI / QG;    // loads each wave issues per staged block, at least
     __shared__ __attribute__((aligned(1024))) char lds[NB * BUF];
 
-    const int lane = threadIdx.x & 63, qw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, qw = QG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, g = lane >> 4;
     // 1-D grid over (head h, query group z, split) items, in that order.  The dispatcher
     // deals consecutive workgroups to the 8 XCDs in turn; when the items divide into
@@ -108,27 +108,28 @@ attn_f16_kernel(AttnArgs a) {
     const int nblk = (a.T + 31) >> 5;
     const int kb0 = split * a.bps, kb1 = min(nblk, kb0 + a.bps);
 
-    // stage block kb into buffer `buf`: slot s -> K plane / V^T plane position
+    // Stage block kb into buffer `buf`: wave load i of a plane is its bytes [1024 i, 1024 i +
+    // 1024), taken by wave i % QG.  Buffer loads from the head's planes (with the
+    // global_load_lds form the compiler waited for every outstanding LDS read at each use
+    // of one); no branch per load (one cost a 16-row window 2 us per launch).
     auto stage = [&](int kb, int buf) {
         const int k0 = kb * 32;
         char* base = lds + buf * BUF;
 #pragma unroll
-        for (int j = 0; j < (NSLOT / 64 + QG - 1) / QG; ++j) {
+        for (int j = 0; j < (KI + QG - 1) / QG; ++j) {       // K: 32 x KCOLS slots
             const int i = qw + j * QG;
-            if (i >= NSLOT / 64) break;
-            const int sl = i * 64 + lane;
-            // buffer loads from the head's planes (with the global_load_lds form the compiler
-            // waited for every outstanding LDS read at each use of one)
-            if (i * 64 < KPLANE / 16) {                  // K: 32 x KCOLS slots
-                const int key = sl / KCOLS, pc = sl % KCOLS;
-                const int col = pc ^ (swz_k(key) & (KCOLS - 1));
-                buffer_to_lds16(Kp, (key * DH + col * 8) * 2, k0 * DH * 2, base + i * 1024);
-            } else {                                     // V^T: DH x 4 slots
-                const int s1 = sl - KPLANE / 16;
-                const int dim = s1 >> 2, pc = s1 & 3;
-                const int col = pc ^ ((dim >> 2) & 3);
-                buffer_to_lds16(Vp, (dim * a.Cs + col * 8) * 2, k0 * 2, base + i * 1024);
-            }
+            if (KI % QG != 0 && i >= KI) break;
+            const int key = (i * 64 + lane) / KCOLS, pc = lane % KCOLS;
+            const int col = pc ^ (swz_k(key) & (KCOLS - 1));
+            buffer_to_lds16(Kp, (key * DH + col * 8) * 2, k0 * DH * 2, base + i * 1024);
+        }
+#pragma unroll
+        for (int j = 0; j < (VI + QG - 1) / QG; ++j) {       // V^T: DH x 4 slots
+            const int i = qw + j * QG;
+            if (VI % QG != 0 && i >= VI) break;
+            const int dim = (i * 64 + lane) >> 2, pc = lane & 3;
+            const int col = pc ^ ((dim >> 2) & 3);
+            buffer_to_lds16(Vp, (dim * a.Cs + col * 8) * 2, k0 * 2, base + KPLANE + i * 1024);
         }
     };
 
@@ -137,15 +138,12 @@ attn_f16_kernel(AttnArgs a) {
     // such care, its scores past T are masked
     auto zero_tail = [&](int kb, int buf) {
         const int k0 = kb * 32;
-        char* base = lds + buf * BUF;
+        char* base = lds + buf * BUF + KPLANE;
 #pragma unroll
-        for (int j = 0; j < (NSLOT / 64 + QG - 1) / QG; ++j) {
+        for (int j = 0; j < (VI + QG - 1) / QG; ++j) {
             const int i = qw + j * QG;
-            if (i >= NSLOT / 64) break;
-            const int sl = i * 64 + lane;
-            if (sl < KPLANE / 16) continue;
-            const int s1 = sl - KPLANE / 16;
-            const int dim = s1 >> 2, pc = s1 & 3;
+            if (VI % QG != 0 && i >= VI) break;
+            const int dim = (i * 64 + lane) >> 2, pc = lane & 3;
             const int key = k0 + 8 * (pc ^ ((dim >> 2) & 3));      // the slot's first key
             if (key + 8 <= a.T) continue;
             u32x4_t* slot = (u32x4_t*)(base + i * 1024 + lane * 16);
