@@ -185,7 +185,10 @@ constexpr int GU_WIDE_TILES = 10;
 // Every GEMM over more than 64 token rows (prompts, wide windows) except the LM head and
 // those of fp32 models runs the LDS-tiled kernel: each weight and activation chunk is
 // fetched once per workgroup and shared by its waves, where the streaming layouts re-read
-// the activations per row group and the weights per 64 rows.
+// the activations per row group and the weights per 64 rows.  int8 from 129 to 192 rows
+// stays with the streaming layouts: those rows are three of their 64-row blocks but two
+// half-filled 128-row tiles, whose widening is not hidden (three layers of the LLaDA-8B
+// shape at 144 rows: 789 against 842 us; at 128 rows 626 and 629, at 208 929 and 864).
 //
 // Which rt x tt tiles a workgroup takes, and how many K slices, is the cheapest of the
 // shapes below under a model of the launch: rounds of workgroups over the chip, each of
@@ -221,19 +224,16 @@ TiledPlan tiled_plan(GemmKind k, int n_tiles, int steps, int m_tiles, long rows,
     return best;
 }
 
-// Row tiles per wave group of each template at mt token tiles.  Q4_0 exceptions:
-// the LM head takes 4, since at 8 its code pipeline, activations and 16
+// Row tiles per wave group of each template at mt token tiles.  Q4_0 exception: the
+// LM head takes 4, since at 8 its code pipeline, activations and 16
 // accumulators per token tile need more than 256 registers and leave one wave per
-// SIMD (LLaDA-8B vocabulary at 32 rows: 119 against 144 us per launch); the
-// gate/up and the split-K projections take 3 past 2 token tiles, where 6 (gate/up)
-// or 4 (down: 47 registers at 4 token tiles) would spill.  bf16 split-K projections
+// SIMD (LLaDA-8B vocabulary at 32 rows: 119 against 144 us per launch).  bf16 split-K projections
 // up to 2 token tiles (the down projection of windows of <= 32 rows) take 8 tiles
 // over 8 K slices instead of 4 over 4: the same 256 workgroups, but every workgroup
 // re-reads the hi/lo activation operand of its K slice through L2, so twice the
 // rows per workgroup halve that traffic (LLaDA-8B down at 32 rows: 28.6 -> 26.8 us
 // per launch with the reduction, against twice the partial sums).
 constexpr int template_fw(GemmKind k, int wt, int mt) {
-    if (wt == WT_Q4 && (k == G_GU || k == G_RES) && mt >= 3) return 3;
     if (wt == WT_BF16 && k == G_RES && mt <= 2) return 8;
     return k == G_QKV ? 3 : (k == G_GU ? 6 : (k == G_LM ? (wt == WT_Q4 ? 4 : 8) : 4));
 }
@@ -243,7 +243,7 @@ int template_nwn(GemmKind k) { return k == G_LM ? 4 : 1; }
 // the streaming layouts.
 Decomp decomp(GemmKind k, int wt, const PackedW& W, int M, int MT, int gy, size_t part_floats) {
     const int n_tiles = W.n_tiles, Mc = gy * MT * 16;
-    if (wt != WT_F32 && k != G_LM && M > 64) {
+    if (wt != WT_F32 && k != G_LM && M > 64 && !(wt == WT_I8 && M > 128 && M <= 192)) {
         const int steps = W.KCw * (kc_of(wt) / 32);
         const TiledPlan p = tiled_plan(k, n_tiles, steps, ceil_div(M, 16), Mc, part_floats);
         return Decomp{false, 0, p.ks, p.rt, p.tt};

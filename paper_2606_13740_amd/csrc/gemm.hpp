@@ -164,6 +164,38 @@ constexpr int activation_depth() {
 }
 
 
+// Q4_0 groups of several row tiles run the branch-free loop of gemm_kernel: it reads the
+// activations in 32-column steps through two register slots (one where a second does not
+// fit) and refills each slot as soon as its products are issued; loads past a wave's range
+// or a group's tiles are sent out of the buffer's bounds, where the hardware returns zeros
+// without a memory access, so that no load stands behind a branch (behind one the compiler
+// cannot count the loads in flight and waits for nearly all of them); and a step's row
+// tiles are fenced from each other (left alone the scheduler unpacks all tiles first and
+// runs out of registers, which had kept gate/up and down at 3 tiles past 32 rows).  Us per
+// launch alone at the LLaDA-8B shapes (gate/up, QKV, down): 32 rows 24.2, 16.5, 15.3 ->
+// 22.0, 14.7, 13.5; 16 rows 19.7, 12.8, 11.6 -> 16.9, 11.5, 10.5; 48 rows 41.3, 21.5, 29.3
+// -> 27.8, 19.2, 17.5.  Three layers at 48 rows 377 -> 312 us.  One-tile O projections
+// (9.5 against 11.1 us) and the LM head keep the other loop.  So do int8 and bf16: the same
+// loop measured 2-7% faster alone at 64 rows and 2-4% slower inside a layer.
+template <int WT, int FW, int NWn>
+constexpr bool fenced_loop() { return WT == WT_Q4 && FW > 1 && NWn == 1; }
+
+// Loads through a buffer descriptor: src (wave-uniform) + voff (per lane) + soff (uniform);
+// voff = OUT_OF_RANGE reads zeros and touches no memory.
+constexpr int OUT_OF_RANGE = (int)0x80000000;
+__device__ __forceinline__ u32x4_t buffer_load16(const void* src, int voff, int soff) {
+    return __builtin_amdgcn_raw_buffer_load_b128(
+        __builtin_amdgcn_make_buffer_rsrc((void*)src, 0, 0x7FFFFFFF, 0x00027000), voff, soff, 0);
+}
+__device__ __forceinline__ u32x2_t buffer_load8_nt(const void* src, int voff, int soff) {
+    return __builtin_amdgcn_raw_buffer_load_b64(
+        __builtin_amdgcn_make_buffer_rsrc((void*)src, 0, 0x7FFFFFFF, 0x00027000), voff, soff, 2);
+}
+__device__ __forceinline__ uint32_t buffer_load4(const void* src, int voff, int soff) {
+    return __builtin_amdgcn_raw_buffer_load_b32(
+        __builtin_amdgcn_make_buffer_rsrc((void*)src, 0, 0x7FFFFFFF, 0x00027000), voff, soff, 0);
+}
+
 // Reduction slots: the largest power of two <= NWk whose slots fit ~150 KiB of LDS (a
 // workgroup of these layouts has its CU to itself).  With one slot per wave the
 // K-slice sums take one write round: LLaDA-8B down at 32 rows (8 slots of 16.5 KiB)
@@ -287,6 +319,126 @@ gemm_kernel(GemmArgs g, Epi epi) {
         [[maybe_unused]] const uint32_t* qsp =
             (WT == WT_Q4) ? (const uint32_t*)g.qs + (size_t)nt0 * g.KCw * 16 + (lane & 15) : nullptr;
 
+        // Folded RMSNorm: each wave sums the partials of tokens wave, wave + NW, ... (one
+        // token per wave at a time): lane l adds partials 4l .. 4l+3 (+ 256 per further
+        // chunk) in order, then a fixed xor tree over the wave, so every workgroup gets
+        // the same bits.  The first four tokens' loads go out before the weight loads
+        // (the waits count loads in issue order, so consuming them later does not wait
+        // for the weight stages).
+        float4 ssq_t[4];
+        auto ssq_load = [&](int j0) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const int j = j0 + b * NW, p = 4 * lane;
+                ssq_t[b] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (j < MR) {
+                    const float* row = g.ssq + (size_t)(mt0 * 16 + j) * g.ssq_ld;
+                    if (p + 3 < g.nssq) {
+                        ssq_t[b] = *(const float4*)(row + p);
+                    } else {
+                        if (p < g.nssq) ssq_t[b].x = row[p];
+                        if (p + 1 < g.nssq) ssq_t[b].y = row[p + 1];
+                        if (p + 2 < g.nssq) ssq_t[b].z = row[p + 2];
+                    }
+                }
+            }
+        };
+        auto ssq_reduce = [&](int j0) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const int j = j0 + b * NW;
+                float v = (ssq_t[b].x + ssq_t[b].y) + (ssq_t[b].z + ssq_t[b].w);
+                for (int c = 256; c < g.nssq; c += 256) {      // d > 4096: further chunks
+                    const float* row = g.ssq + (size_t)(mt0 * 16 + min(j, MR - 1)) * g.ssq_ld + c;
+                    for (int e = 0; e < 4; ++e)
+                        if (j < MR && c + 4 * lane + e < g.nssq) v += row[4 * lane + e];
+                }
+                v = warp_sum(v);
+                if (j < MR && lane == 0) rs_sm[j] = 1.0f / sqrtf(v / (float)g.dnorm + g.eps);
+            }
+        };
+        auto ssq_finish = [&]() {
+            if (g.ssq == nullptr) return;
+            ssq_reduce(wave);
+            for (int j0 = wave + 4 * NW; j0 < MR; j0 += 4 * NW) {
+                ssq_load(j0);
+                ssq_reduce(j0);
+            }
+        };
+        if constexpr (fenced_loop<WT, FW, NWn>()) {
+            constexpr int XS = (MT == 4 && FW > 4) ? 1 : 2;   // activation slots of one 32-column step
+            // wave-uniform K range, in scalar registers
+            const int f0 = __builtin_amdgcn_readfirstlane(c0), f1 = __builtin_amdgcn_readfirstlane(c1);
+            u32x2_t wq[FW];                        // codes of a chunk
+            uint32_t wsc[FW];                      // its scales (two fp16)
+            u32x4_t xb[XS][2 * MT];
+            const char* const wsrc = (const char*)g.W + (size_t)nt0 * g.KCw * WCB;
+            const char* const xsrc = (const char*)g.X + (size_t)mt0 * g.KCx * XB;
+            const char* const qsrc = (const char*)g.qs + (size_t)nt0 * g.KCw * 64;
+            auto loadw = [&](int c) {
+#pragma unroll
+                for (int f = 0; f < FW; ++f) {
+                    const bool in = c < f1 && f < nf;
+                    wq[f] = buffer_load8_nt(wsrc, in ? lane * 8 : OUT_OF_RANGE, (f * g.KCw + c) * WCB);
+                    wsc[f] = buffer_load4(qsrc, in ? (lane & 15) * 4 : OUT_OF_RANGE, (f * g.KCw + c) * 64);
+                }
+            };
+            // step st = 2 * chunk + 32-column half
+            auto loadx = [&](int slot, int st) {
+                const int vo = st < 2 * f1 ? lane * 16 : OUT_OF_RANGE;
+#pragma unroll
+                for (int t = 0; t < MT; ++t) {
+                    const int so = (t * g.KCx + st) * XB;
+                    xb[slot][2 * t] = buffer_load16(xsrc, vo, so);
+                    xb[slot][2 * t + 1] = buffer_load16(xsrc, vo, so + 1024);
+                }
+            };
+            auto compute = [&](int h) {            // as in the other loop's compute
+                const u32x4_t* x = xb[h % XS];
+                const u32x4_t ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};   // bf16 1.0
+                f32x4_t zp[MT];
+#pragma unroll
+                for (int t = 0; t < MT; ++t) {
+                    f32x4_t z = mfma_bf16(x[2 * t], ones, f32x4_t{0.f, 0.f, 0.f, 0.f});
+                    z = mfma_bf16(x[2 * t + 1], ones, z);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) zp[t][i] = -136.0f * z[i];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int f = 0; f < FW; ++f) {
+                    const u32x4_t w = q4_unpack(wq[f][h]);
+                    const float sc = f16_bits_to_f32(h == 0 ? (wsc[f] & 0xFFFFu) : (wsc[f] >> 16));
+#pragma unroll
+                    for (int t = 0; t < MT; ++t) {
+                        f32x4_t v = mfma_bf16(x[2 * t], w, zp[t]);
+                        v = mfma_bf16(x[2 * t + 1], w, v);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[f][t][i] = fmaf(sc, v[i], acc[f][t][i]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            if (g.ssq != nullptr) ssq_load(wave);
+            const bool work = f1 > f0 && nf > 0;
+            if (work) {
+#pragma unroll
+                for (int h = 0; h < XS; ++h) loadx(h, 2 * f0 + h);
+                loadw(f0);
+            }
+            stage_prologue();
+            ssq_finish();
+            if (work) {
+                for (int c = f0; c < f1; ++c) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        compute(h);
+                        loadx(h % XS, 2 * c + h + XS);
+                        if (h == 1) loadw(c + 1);
+                    }
+                }
+            }
+        } else {
         u32x4_t wb[D][FW];                    // weight chunks (bf16 / int8 / fp32)
         [[maybe_unused]] u32x2_t wq[D][FW];   // Q4_0 codes
         [[maybe_unused]] uint32_t wsc[D][FW]; // Q4_0 scales (two fp16)
@@ -399,44 +551,6 @@ gemm_kernel(GemmArgs g, Epi epi) {
                     wb[s][f] = u32x4_t{0u, 0u, 0u, 0u};
                 }
             }
-        // Folded RMSNorm: each wave sums the partials of tokens wave, wave + NW, ... (one
-        // token per wave at a time): lane l adds partials 4l .. 4l+3 (+ 256 per further
-        // chunk) in order, then a fixed xor tree over the wave, so every workgroup gets
-        // the same bits.  The first four tokens' loads go out before the weight loads
-        // (the waits count loads in issue order, so consuming them later does not wait
-        // for the weight stages).
-        float4 ssq_t[4];
-        auto ssq_load = [&](int j0) {
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const int j = j0 + b * NW, p = 4 * lane;
-                ssq_t[b] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (j < MR) {
-                    const float* row = g.ssq + (size_t)(mt0 * 16 + j) * g.ssq_ld;
-                    if (p + 3 < g.nssq) {
-                        ssq_t[b] = *(const float4*)(row + p);
-                    } else {
-                        if (p < g.nssq) ssq_t[b].x = row[p];
-                        if (p + 1 < g.nssq) ssq_t[b].y = row[p + 1];
-                        if (p + 2 < g.nssq) ssq_t[b].z = row[p + 2];
-                    }
-                }
-            }
-        };
-        auto ssq_reduce = [&](int j0) {
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const int j = j0 + b * NW;
-                float v = (ssq_t[b].x + ssq_t[b].y) + (ssq_t[b].z + ssq_t[b].w);
-                for (int c = 256; c < g.nssq; c += 256) {      // d > 4096: further chunks
-                    const float* row = g.ssq + (size_t)(mt0 * 16 + min(j, MR - 1)) * g.ssq_ld + c;
-                    for (int e = 0; e < 4; ++e)
-                        if (j < MR && c + 4 * lane + e < g.nssq) v += row[4 * lane + e];
-                }
-                v = warp_sum(v);
-                if (j < MR && lane == 0) rs_sm[j] = 1.0f / sqrtf(v / (float)g.dnorm + g.eps);
-            }
-        };
         if (g.ssq != nullptr) ssq_load(wave);
         const bool work = c1 > c0 && nf > 0;
         if (work) {
@@ -447,13 +561,7 @@ gemm_kernel(GemmArgs g, Epi epi) {
             }
         }
         stage_prologue();
-        if (g.ssq != nullptr) {
-            ssq_reduce(wave);
-            for (int j0 = wave + 4 * NW; j0 < MR; j0 += 4 * NW) {
-                ssq_load(j0);
-                ssq_reduce(j0);
-            }
-        }
+        ssq_finish();
         if (work) {
             // chunk c uses weight slot c % D and activation slot c % DX (DX divides D).
             // For a group that fills the template, rounds whose D successors all lie
@@ -501,6 +609,7 @@ gemm_kernel(GemmArgs g, Epi epi) {
                     if (c + DX < c1) loadx(sx, c + DX);
                 }
             }
+        }
         }
     }
 
