@@ -408,55 +408,95 @@ __global__ void __launch_bounds__(32 * ATTN_MERGE_PAIRS) attn_combine_kernel(Att
     xfrag_store4<XF32>(a.o, row, h * DH + d0, a.KCx, make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv));
 }
 
-// fp32 path (small models): one wave per (row, head); lanes stride over keys with
-// a lane-local online softmax, merged across lanes by a butterfly.
+// fp32 path (small models): one workgroup of 4 waves per (row, head); wave w takes 64-key
+// chunks w, w + 4, ...  A chunk's scores have one key per lane, its output one dim (DH 128:
+// two) per lane with the probabilities broadcast from LDS; the waves' states are merged in
+// wave order.  Latency-bound: with a key per lane in both halves, the butterfly that merged
+// 64 lanes' O vectors was most of the time (32 rows, 4 heads of 64, 96 keys: 57 -> 6.9 us).
+constexpr int ATTN_F32_WAVES = 4;
 template <int DH>
-__global__ void __launch_bounds__(64) attn_f32_kernel(AttnArgs a) {
-    const int lane = threadIdx.x;
+__global__ void __launch_bounds__(64 * ATTN_F32_WAVES) attn_f32_kernel(AttnArgs a) {
+    constexpr int NW = ATTN_F32_WAVES, ND = (DH + 63) / 64;
+    __shared__ __attribute__((aligned(16))) float q_s[DH];
+    __shared__ __attribute__((aligned(16))) float p_s[NW][64];
+    __shared__ float o_s[NW][DH], m_s[NW], l_s[NW];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int row = blockIdx.x, h = blockIdx.y;
-    const int ld = a.H * DH;
-    const float* qp = (const float*)a.q + (size_t)row * ld + h * DH;
     const int hk = h / a.G;                                  // K/V head of this query head
     const float* Kp = (const float*)a.K + (size_t)hk * a.Cs * DH;
     const float* Vp = (const float*)a.Vt + (size_t)hk * DH * a.Cs;
     const int lim = (a.lim != nullptr && row < a.M) ? a.lim[row] : a.T;
+    if (threadIdx.x < DH) q_s[threadIdx.x] = ((const float*)a.q)[(size_t)row * a.H * DH + h * DH + threadIdx.x];
+    __syncthreads();
 
-    float q[DH];
+    float m = -INFINITY, l = 0.f;                            // the same in every lane
+    float o[ND];
 #pragma unroll
-    for (int j = 0; j < DH; ++j) q[j] = qp[j];
-    float m = -INFINITY, l = 0.f;
-    float o[DH];
+    for (int d = 0; d < ND; ++d) o[d] = 0.f;
+    for (int k0 = 64 * wave; k0 < lim; k0 += 64 * NW) {
+        const int n = min(64, lim - k0);                     // keys past the limit are never read
+        float s = -INFINITY;
+        if (lane < n) {
+            const float4* kr = (const float4*)(Kp + (size_t)(k0 + lane) * DH);
+            s = 0.f;
 #pragma unroll
-    for (int j = 0; j < DH; ++j) o[j] = 0.f;
-    for (int k = lane; k < lim; k += 64) {
-        const float* kr = Kp + (size_t)k * DH;
-        float s = 0.f;
-#pragma unroll
-        for (int j = 0; j < DH; ++j) s = fmaf(q[j], kr[j], s);
-        s *= a.scale;
-        const float mn = fmaxf(m, s);
+            for (int j = 0; j < DH / 4; ++j) {
+                const float4 kv = kr[j], qv = *(const float4*)(q_s + 4 * j);
+                s = fmaf(qv.x, kv.x, s);
+                s = fmaf(qv.y, kv.y, s);
+                s = fmaf(qv.z, kv.z, s);
+                s = fmaf(qv.w, kv.w, s);
+            }
+            s *= a.scale;
+        }
+        const float mn = fmaxf(m, warp_max(s));
         const float alpha = expf(m - mn);
-        const float p = expf(s - mn);
-        l = l * alpha + p;
-#pragma unroll
-        for (int j = 0; j < DH; ++j) o[j] = o[j] * alpha + p * Vp[(size_t)j * a.Cs + k];
+        const float p = lane < n ? expf(s - mn) : 0.f;
+        l = l * alpha + warp_sum(p);
         m = mn;
+        p_s[wave][lane] = p;                                 // read back by the same wave only
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int d = 0; d < ND; ++d) {
+            const int dim = lane + 64 * d;
+            if (dim >= DH) break;
+            const float* vr = Vp + (size_t)dim * a.Cs + k0;
+            float acc = o[d] * alpha;
+            int j = 0;
+#pragma unroll 8
+            for (; j + 4 <= n; j += 4) {
+                const float4 vv = *(const float4*)(vr + j), pv = *(const float4*)(p_s[wave] + j);
+                acc = fmaf(pv.x, vv.x, acc);
+                acc = fmaf(pv.y, vv.y, acc);
+                acc = fmaf(pv.z, vv.z, acc);
+                acc = fmaf(pv.w, vv.w, acc);
+            }
+            for (; j < n; ++j) acc = fmaf(p_s[wave][j], vr[j], acc);
+            o[d] = acc;
+        }
+        __builtin_amdgcn_wave_barrier();
     }
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const float m2 = __shfl_xor(m, off), l2 = __shfl_xor(l, off);
-        const float mn = fmaxf(m, m2);
-        const float w1 = (m == -INFINITY) ? 0.f : expf(m - mn);
-        const float w2 = (m2 == -INFINITY) ? 0.f : expf(m2 - mn);
-        l = l * w1 + l2 * w2;
-#pragma unroll
-        for (int j = 0; j < DH; ++j) o[j] = o[j] * w1 + __shfl_xor(o[j], off) * w2;
-        m = mn;
+    for (int d = 0; d < ND; ++d)
+        if (lane + 64 * d < DH) o_s[wave][lane + 64 * d] = o[d];
+    if (lane == 0) {
+        m_s[wave] = m;
+        l_s[wave] = l;
     }
-    const float inv = 1.f / l;
+    __syncthreads();
+    if (threadIdx.x < DH) {
+        float mx = m_s[0];                                   // wave 0 always has a key
 #pragma unroll
-    for (int j = 0; j < DH; ++j)
-        if ((j & 63) == lane) xfrag_store<true>(a.o, row, h * DH + j, a.KCx, o[j] * inv);
+        for (int w = 1; w < NW; ++w) mx = fmaxf(mx, m_s[w]);
+        float L = 0.f, ov = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float e = expf(m_s[w] - mx);               // 0 for a wave without keys
+            L += l_s[w] * e;
+            ov += o_s[w][threadIdx.x] * e;
+        }
+        xfrag_store<true>(a.o, row, h * DH + threadIdx.x, a.KCx, ov / L);
+    }
 }
 
 }  // namespace dllm

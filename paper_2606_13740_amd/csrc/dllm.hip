@@ -687,9 +687,9 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
             ProbeScope ps(m, DLLM_K_ATTN, s);
             if (XF32) {
                 at.nsplit = 1; at.bps = 1 << 20;
-                if (Dh == 32) hipLaunchKernelGGL((attn_f32_kernel<32>), dim3(Mc, H), dim3(64), 0, s, at);
-                else if (Dh == 64) hipLaunchKernelGGL((attn_f32_kernel<64>), dim3(Mc, H), dim3(64), 0, s, at);
-                else hipLaunchKernelGGL((attn_f32_kernel<128>), dim3(Mc, H), dim3(64), 0, s, at);
+                if (Dh == 32) hipLaunchKernelGGL((attn_f32_kernel<32>), dim3(Mc, H), dim3(64 * ATTN_F32_WAVES), 0, s, at);
+                else if (Dh == 64) hipLaunchKernelGGL((attn_f32_kernel<64>), dim3(Mc, H), dim3(64 * ATTN_F32_WAVES), 0, s, at);
+                else hipLaunchKernelGGL((attn_f32_kernel<128>), dim3(Mc, H), dim3(64 * ATTN_F32_WAVES), 0, s, at);
             } else {
                 // One wave per query tile, up to 4 tiles sharing each staged K/V block; from
                 // 512 workgroups of twice that (long prompts) two tiles per wave, which halve
