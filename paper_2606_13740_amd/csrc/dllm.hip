@@ -1164,8 +1164,12 @@ int dllm_commit(const float* d_conf, const int32_t* d_id, int32_t* d_tok, uint8_
     if (!d_conf || !d_id || !d_tok || !d_mask) return fail(DLLM_E_INVAL, "NULL argument");
     if (k < 0) return fail(DLLM_E_INVAL, "k must be >= 0");
     if (seg_begin < 0 || seg_len < 0 || seg_len > 1024) return fail(DLLM_E_INVAL, "segment out of range");
-    hipLaunchKernelGGL(commit_kernel, dim3(1), dim3(256), 0, (hipStream_t)stream, d_conf, d_id, d_tok, d_mask,
-                       seg_begin, seg_len, k, d_committed_pos, d_n_committed);
+    if (seg_len <= 64)
+        hipLaunchKernelGGL(commit_wave_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, d_conf, d_id, d_tok, d_mask,
+                           seg_begin, seg_len, k, d_committed_pos, d_n_committed);
+    else
+        hipLaunchKernelGGL(commit_kernel, dim3(1), dim3(256), 0, (hipStream_t)stream, d_conf, d_id, d_tok, d_mask,
+                           seg_begin, seg_len, k, d_committed_pos, d_n_committed);
     HIP_TRY(hipGetLastError());
     return DLLM_OK;
 }

@@ -298,6 +298,32 @@ commit_kernel(const float* conf, const int* id, int* tok, uint8_t* mask, int seg
     if (threadIdx.x == 0 && n_committed) *n_committed = min(k, cnt);
 }
 
+// The same for segments of at most 64 positions: one wave, a position per lane, every load
+// in one round, the masked positions' confidences compared lane by lane (a 32-row block:
+// 6.8 -> 5.0 us per launch).
+__global__ void __launch_bounds__(64)
+commit_wave_kernel(const float* conf, const int* id, int* tok, uint8_t* mask, int seg_begin, int seg_len,
+                   int k, int* committed, int* n_committed) {
+    const int lane = threadIdx.x, p = seg_begin + lane;
+    const bool in = lane < seg_len;
+    const bool masked = in && mask[p] != 0;
+    const float c = in ? conf[p] : 0.f;
+    const int pid = in ? id[p] : 0;
+    const unsigned long long all = __ballot(masked);
+    int rank = 0;
+    for (unsigned long long left = all; left != 0; left &= left - 1) {
+        const int j = __ffsll(left) - 1;
+        const float cj = __shfl(c, j);
+        if (cj > c || (cj == c && j < lane)) ++rank;
+    }
+    if (masked && rank < k) {
+        tok[p] = pid;
+        mask[p] = 0;
+        if (committed) committed[rank] = p;
+    }
+    if (lane == 0 && n_committed) *n_committed = min(k, (int)__popcll(all));
+}
+
 // ---------------------------------------------------------------------------
 // Staged token stabilisation over one segment (one thread per position, <= 1024):
 // state 0 invisible (masked), 1 visible, 2 stable.  Invisible positions at or
