@@ -140,6 +140,10 @@ namespace {
 // Launch configuration of the weight-streaming GEMMs
 // ---------------------------------------------------------------------------
 
+// Waves of a small model's one-tile workgroups, K over them: latency-bound, so as many as
+// still have a chunk each (two fp32 layers of d 256, 32 rows: 91 us per step with 8, 99 with 4).
+constexpr int SMALL_WAVES = 8;
+
 enum GemmKind { G_QKV = 0, G_RES = 1, G_GU = 2, G_LM = 3 };
 
 int kc_of(int wt) { return wt == WT_F32 ? 16 : (wt == WT_BF16 ? 32 : 64); }
@@ -343,7 +347,7 @@ int launch_gemm(const Decomp& dc, int M, int MT, const GemmArgs& g0, const Epi& 
             return launch_tiled<WT>(dc, g, epi, m_tiles, s);
         }
     }
-    if (dc.small) return launch_gemm_mt<WT, -1, 1, 4>(MT, g, epi, n_tiles, dc.ks, gy, s);
+    if (dc.small) return launch_gemm_mt<WT, -1, 1, SMALL_WAVES>(MT, g, epi, n_tiles, dc.ks, gy, s);
     if constexpr (KIND == G_GU && WT == WT_BF16) {
         if (g.tpg > template_fw(G_GU, WT, MT)) {
             if (g.tpg > GU_WIDE_TILES || MT > 2) return fail(DLLM_E_INVAL, "internal: gate/up tiles outside the templates");
@@ -639,10 +643,13 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
     // operand at each kept row's slot, which the embedding kernel records.
     const bool fused = (gy == 1);
     // The down projection keeps split-K + the reduction kernel (which writes the
-    // normalised operand): over the whole K range each of its workgroups would read the
-    // whole 12288-wide activation (4x the L2 traffic of 4 split-K slices).  QKV then
-    // reads a normalised operand, except after the embedding (layer 0), which folds.
-    constexpr bool FUSE_DOWN = false;
+    // normalised operand) where it splits: over the whole K range each of its workgroups
+    // would read the whole 12288-wide activation (4x the L2 traffic of 4 split-K slices).
+    // QKV then reads a normalised operand, except after the embedding (layer 0), which
+    // folds.  Models small enough for one slice fold it like the O projection, which saves
+    // the reduction's launch (two fp32 layers of d 256: 4.7 of ~50 us per layer).
+    const bool fuse_down =
+        fused && decomp(G_RES, WT, m->layers[0].down, a.M, MT, gy, w.part_floats).small;
     const bool lm_sel_last = a.lm && a.sel;
     auto nssq_qkv = [&](int l) { return l == 0 ? 1 : m->layers[l - 1].down.n_tiles; };
 
@@ -670,7 +677,7 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
         if (run(DLLM_K_QKV)) {
             GemmArgs g{L.qkv.w, L.qkv.scale, w.xg, L.qkv.KCw, L.qkv.KCw * WTraits<WT>::XPER, L.qkv.n_tiles, L.bqkv};
             g.qs = L.qkv.qs;
-            if (fused && (l == 0 || FUSE_DOWN)) fold_norm(g, m, w, nssq_qkv(l));
+            if (fused && (l == 0 || fuse_down)) fold_norm(g, m, w, nssq_qkv(l));
             EpiQKV<XF32> e{d, m->dkv, Dh, a.M, a.pos_base, a.pos, m->rope, (AT*)w.q, q_plane, Kc, Vt, kv->Cs};
             ProbeScope ps(m, DLLM_K_QKV, s);
             if ((rc = launch_gemm<WT, G_QKV>(decomp(G_QKV, WT, L.qkv, a.M, MT, gy, w.part_floats), a.M, MT, g, e, gy, s,
@@ -753,7 +760,7 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
             const float* gnext = last ? m->gf : m->layers[l + 1].g1;
             const bool sel = last && lm_sel_last;
             ProbeScope ps(m, DLLM_K_DOWN, s);
-            if (fused && FUSE_DOWN) {
+            if (fuse_down) {
                 if ((rc = residual_proj_fused<WT, XF32>(m, w, L.down, w.af, gnext, a.M, MT, s, sel ? w.slot : nullptr)))
                     return rc;
             } else if ((rc = residual_proj<WT, XF32>(m, w, L.down, w.af, gnext, a.M, Mc, MT, gy, s, sel, a.need,
@@ -774,7 +781,7 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
         if (gyl * MTl * 16 > w.wrows) return fail(DLLM_E_INVAL, "LM head rows exceed the window workspace");
         GemmArgs g{m->lm.w, m->lm.scale, w.xg, m->lm.KCw, m->lm.KCw * WTraits<WT>::XPER, m->lm.n_tiles};
         g.qs = m->lm.qs;
-        if (fused && FUSE_DOWN) fold_norm(g, m, w, m->layers[c.n_layers - 1].down.n_tiles);
+        if (fuse_down) fold_norm(g, m, w, m->layers[c.n_layers - 1].down.n_tiles);
         const Decomp dc = decomp(G_LM, WT, m->lm, Ml, MTl, gyl, 0);
         const int gx = row_groups(dc, m->lm.n_tiles);
         if (gx > m->n_lm_wg) return fail(DLLM_E_INVAL, "internal: LM-head partials exceed their buffer");
