@@ -200,13 +200,14 @@ constexpr int GU_WIDE_TILES = 10;
 // 16 x 16 tile, plus the partial sums that K slices write and the finish reads.  In units
 // of 4.2 ns, measured (bf16, one round): a step of 16 x 16 tiles 1.29 us, 12 x 16 1.17,
 // 16 x 8 0.79, 12 x 8 0.67, 8 x 8 0.48 alone on a CU and 0.89 for two (its 80 KiB of LDS
-// let two workgroups share one).  int8 and Q4_0 steps take longer in the same proportion.
+// let two workgroups share one), 6 x 8 0.52 on all CUs (gate/up at 128 rows: 66 us against
+// 69 with 8 x 8 on 192 CUs).  int8 and Q4_0 steps take longer in the same proportion.
 // It picks, at the LLaDA-8B widths, 16 x 16 at 4096 rows, 12 x 16 for gate/up at 512
 // rows (256 workgroups in one round, 149 us; 16 x 16 fills 192 CUs: 166), 12 x 8 for
 // gate/up at 200 rows (86 us; 16 x 16: 168), K slices for O and down.
 struct TiledPlan { int rt, tt, ks; };
 TiledPlan tiled_plan(GemmKind k, int n_tiles, int steps, int m_tiles, long rows, size_t part_floats) {
-    static constexpr int shapes[][2] = {{16, 16}, {12, 16}, {16, 8}, {12, 8}, {8, 8}};
+    static constexpr int shapes[][2] = {{16, 16}, {12, 16}, {16, 8}, {12, 8}, {8, 8}, {6, 8}};
     TiledPlan best{16, 16, 1};
     double best_cost = 1e30;
     for (const auto& sh : shapes) {
@@ -215,7 +216,7 @@ TiledPlan tiled_plan(GemmKind k, int n_tiles, int steps, int m_tiles, long rows,
             const double out = (double)n_tiles * 16 * rows;          // outputs (padded rows)
             if (ks > 1 && out * ks > (double)part_floats) break;
             const long wgs = (long)ceil_div(n_tiles, rt) * ks * ceil_div(m_tiles, tt);
-            double step = 60 + rt * tt;
+            double step = rt * tt == 48 ? 120 : 60 + rt * tt;
             long rounds = ceil_div(wgs, N_CU);
             if (rt * tt == 64 && wgs > N_CU) { rounds = ceil_div(wgs, 2 * N_CU); step = 212; }
             // O / down write and read their sums whatever ks is; QKV only with K slices.
@@ -315,6 +316,7 @@ int launch_tiled(const Decomp& dc, const GemmArgs& g, const Epi& epi, int m_tile
     else if (dc.rt == 16 && dc.tt == 8) launch_tiled_inst<WT, 16, 8>(g, epi, dc.ks, m_tiles, s);
     else if (dc.rt == 12 && dc.tt == 8) launch_tiled_inst<WT, 12, 8>(g, epi, dc.ks, m_tiles, s);
     else if (dc.rt == 8 && dc.tt == 8) launch_tiled_inst<WT, 8, 8>(g, epi, dc.ks, m_tiles, s);
+    else if (dc.rt == 6 && dc.tt == 8) launch_tiled_inst<WT, 6, 8>(g, epi, dc.ks, m_tiles, s);
     else return fail(DLLM_E_INVAL, "internal: no tiled GEMM of this shape");
     return DLLM_OK;
 }
@@ -338,7 +340,7 @@ int launch_gemm(const Decomp& dc, int M, int MT, const GemmArgs& g0, const Epi& 
                     g.bias = nullptr;
                     const EpiPartial ep{part, N, rows};
                     if (int rc = launch_tiled<WT>(dc, g, ep, m_tiles, s)) return rc;
-                    hipLaunchKernelGGL((split_epilogue_kernel<Epi>), dim3(ceil_div(n_tiles, 16), ceil_div(m_tiles, 4)),
+                    hipLaunchKernelGGL((split_epilogue_kernel<Epi>), dim3(ceil_div(n_tiles, SPLIT_EPI_RT), ceil_div(m_tiles, SPLIT_EPI_WM)),
                                        dim3(256), 0, s, (const float*)part, dc.ks, rows, N, n_tiles, m_tiles, g0.bias,
                                        epi);
                     return DLLM_OK;

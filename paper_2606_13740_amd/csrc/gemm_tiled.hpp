@@ -162,19 +162,19 @@ __global__ void __launch_bounds__(512) gemm_tiled_kernel(GemmArgs g, Epi epi, in
         };
         // the products of row tile f with the wave's token tiles
         [[maybe_unused]] f32x4_t zp[T::WM];
-        auto products = [&](int f, int h, const u32x4_t* xs) {
+        auto products = [&](int f, int h, const u32x4_t* xs, const u32x4_t& cur) {
             u32x4_t w;
             if constexpr (WT == WT_Q4) {
                 w = q4_unpack(held[f][h]);
             } else if constexpr (WT == WT_I8) {
                 if (h == 0) {
-                    w = i8x8_to_bf16x8(raw[f & 1][0], raw[f & 1][1]);
-                    held[f] = u32x2_t{raw[f & 1][2], raw[f & 1][3]};
+                    w = i8x8_to_bf16x8(cur[0], cur[1]);
+                    held[f] = u32x2_t{cur[2], cur[3]};
                 } else {
                     w = i8x8_to_bf16x8(held[f][0], held[f][1]);
                 }
             } else {
-                w = raw[f & 1];
+                w = cur;
             }
             if constexpr (WT == WT_Q4) {
                 const float sc = f16_bits_to_f32(h == 0 ? (hsc[f] & 0xFFFFu) : (hsc[f] >> 16));
@@ -239,6 +239,7 @@ __global__ void __launch_bounds__(512) gemm_tiled_kernel(GemmArgs g, Epi epi, in
                         stage_x(i + u + 3, xs);
                         __builtin_amdgcn_sched_barrier(0);
                     }
+                    const u32x4_t cur = raw[f & 1];    // (an odd WR reads the next step's first tile into it)
                     if (f + 1 < T::WR) read_w(f + 1, h, ws);
                     else read_w(0, XPER == 1 ? 0 : h ^ 1, wnext);
                     if (f >= F1) {
@@ -246,7 +247,7 @@ __global__ void __launch_bounds__(512) gemm_tiled_kernel(GemmArgs g, Epi epi, in
                         for (int j = 0; j < XPF; ++j)
                             if ((f - F1) * XPF + j < T::WM) read_x(x[u ^ 1], (f - F1) * XPF + j, xnext);
                     }
-                    products(f, h, x[u]);
+                    products(f, h, x[u], cur);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 xs = xnext;
@@ -304,33 +305,53 @@ __global__ void __launch_bounds__(512) gemm_tiled_kernel(GemmArgs g, Epi epi, in
 }
 
 // Split-K finish of the tiled kernel for the QKV projection of short prompts (whose
-// 256 x 256 tiles alone leave the chip half idle): each workgroup sums the KS partial
-// slices P[s][m][n] of a 256-row x 64-token block in slice order into an LDS tile,
-// adds the bias once, and runs the projection's epilogue on it, as the tiled kernel
-// does with its own sums.
+// tiles alone leave the chip half idle): each workgroup sums the KS partial slices
+// P[s][m][n] of a 128-row x 32-token block in slice order into an LDS tile, adds the bias
+// once, and runs the projection's epilogue on it, as the tiled kernel does with its own
+// sums.  Bound by the latency of its loads: small blocks, so that every CU has several,
+// and four loads per thread and slice in flight (200 rows, 2 slices: 18.6 us with one
+// load at a time over 256 x 64 blocks).
+constexpr int SPLIT_EPI_RT = 8, SPLIT_EPI_WM = 2;   // row tiles x token tiles per workgroup
 template <class Epi>
 __global__ void __launch_bounds__(256) split_epilogue_kernel(const float* P, int ks, int rows, int ldn, int n_tiles,
                                                              int m_tiles, const float* bias, Epi epi) {
-    constexpr int RT = 16, WM = 4, LDY = 16 * RT + 4;
+    constexpr int RT = SPLIT_EPI_RT, WM = SPLIT_EPI_WM, LDY = 16 * RT + 4;
     __shared__ __attribute__((aligned(16))) float Y[16 * WM * LDY];
     const int nt0 = blockIdx.x * RT, mt0 = blockIdx.y * WM;
     const int nrows = 16 * min(RT, n_tiles - nt0), mcols = 16 * min(WM, m_tiles - mt0);
     const int n0 = nt0 * 16, m0 = mt0 * 16;
     const size_t slice = (size_t)rows * ldn;
-    // four consecutive outputs of one token per thread (16-byte loads along P's rows)
-    const int nq = nrows >> 2;
-    for (int idx = threadIdx.x; idx < nq * mcols; idx += blockDim.x) {
-        const int qd = idx % nq, ml = idx / nq, nl = 4 * qd;
-        const float* p = P + (size_t)(m0 + ml) * ldn + n0 + nl;
-        float4 v = *(const float4*)p;
-        for (int k = 1; k < ks; ++k) {
-            const float4 u = *(const float4*)(p + k * slice);
-            v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+    // four consecutive outputs of one token per item (16-byte loads along P's rows), U items
+    // per thread in flight
+    constexpr int U = 4;
+    const int nq = nrows >> 2, nitems = nq * mcols;
+    for (int base = threadIdx.x; base < nitems; base += U * blockDim.x) {
+        const float* p[U];
+        float4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int idx = min(base + u * (int)blockDim.x, nitems - 1);   // past the end: the last item again
+            p[u] = P + (size_t)(m0 + idx / nq) * ldn + n0 + 4 * (idx % nq);
+            v[u] = *(const float4*)p[u];
         }
-        if (bias != nullptr) {
-            v.x += bias[n0 + nl]; v.y += bias[n0 + nl + 1]; v.z += bias[n0 + nl + 2]; v.w += bias[n0 + nl + 3];
+#pragma unroll 3
+        for (int k = 1; k < ks; ++k)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float4 w = *(const float4*)(p[u] + k * slice);
+                v[u].x += w.x; v[u].y += w.y; v[u].z += w.z; v[u].w += w.w;
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int idx = base + u * (int)blockDim.x;
+            if (idx >= nitems) break;
+            const int nl = 4 * (idx % nq), ml = idx / nq;
+            if (bias != nullptr) {
+                const float4 bv = *(const float4*)(bias + n0 + nl);
+                v[u].x += bv.x; v[u].y += bv.y; v[u].z += bv.z; v[u].w += bv.w;
+            }
+            *(float4*)(Y + ml * LDY + nl) = v[u];
         }
-        *(float4*)(Y + ml * LDY + nl) = v;
     }
     __syncthreads();
     epi(YTokens<LDY>{Y}, n0, nrows, m0, mcols, blockIdx.x, nullptr, NoScale{});
