@@ -205,7 +205,15 @@ constexpr int GU_WIDE_TILES = 10;
 // It picks, at the LLaDA-8B widths, 16 x 16 at 4096 rows, 12 x 16 for gate/up at 512
 // rows (256 workgroups in one round, 149 us; 16 x 16 fills 192 CUs: 166), 12 x 8 for
 // gate/up at 200 rows (86 us; 16 x 16: 168), K slices for O and down.
+//
+// The plan decides the order of the sums, so it depends on the model's widths and the
+// call's rows only, never on the workspace at hand (which grows with the longest prompt
+// seen, and is the static scratch in the no-allocation step).
 struct TiledPlan { int rt, tt, ks; };
+
+// Split-K partial sums, in units of d_model floats, that every workspace holds for a call
+// of Mc padded rows (part_floats_for gives at least as many).
+long part_rows(long Mc) { return std::max(Mc, std::min(8 * Mc, 4096L)); }
 TiledPlan tiled_plan(GemmKind k, int n_tiles, int steps, int m_tiles, long rows, size_t part_floats) {
     static constexpr int shapes[][2] = {{16, 16}, {12, 16}, {16, 8}, {12, 8}, {8, 8}, {6, 8}};
     TiledPlan best{16, 16, 1};
@@ -245,12 +253,12 @@ constexpr int template_fw(GemmKind k, int wt, int mt) {
 int template_nwn(GemmKind k) { return k == G_LM ? 4 : 1; }
 
 // W: the packed operand of M token rows, computed as gy blocks of MT tiles (Mc rows) by
-// the streaming layouts.
-Decomp decomp(GemmKind k, int wt, const PackedW& W, int M, int MT, int gy, size_t part_floats) {
+// the streaming layouts.  d: d_model.
+Decomp decomp(GemmKind k, int wt, const PackedW& W, int M, int MT, int gy, int d) {
     const int n_tiles = W.n_tiles, Mc = gy * MT * 16;
     if (wt != WT_F32 && k != G_LM && M > 64 && !(wt == WT_I8 && M > 128 && M <= 192)) {
         const int steps = W.KCw * (kc_of(wt) / 32);
-        const TiledPlan p = tiled_plan(k, n_tiles, steps, ceil_div(M, 16), Mc, part_floats);
+        const TiledPlan p = tiled_plan(k, n_tiles, steps, ceil_div(M, 16), Mc, (size_t)part_rows(Mc) * d);
         return Decomp{false, 0, p.ks, p.rt, p.tt};
     }
     const int min_tiles = (k == G_QKV || k == G_RES) ? 128 : (k == G_GU ? 256 : 512);
@@ -407,10 +415,10 @@ int alloc_zero(void** p, size_t bytes) {
 // own, grown on demand, and the no-allocation step's static scratch) is carved here.
 size_t ws_carve(const dllm_model* m, int rows, int wrows, size_t part_floats, char* base, Workspace* w);
 
-// Split-K partials: 4 slices of the window rows (streaming layouts), or up to 8 slices
-// of 256+ token rows (tiled layout), at most 4096 rows.
+// Split-K partials: RES_SPLIT slices of the window rows (O and down of up to 64 rows), and
+// what the tiled layouts of up to `rows` rows plan with (QKV, O and down past 64 rows).
 size_t part_floats_for(const dllm_model* m, int rows, int wrows) {
-    return (size_t)std::max({RES_SPLIT * wrows, rows, std::min(8 * rows, 4096)}) * m->cfg.d_model;
+    return (size_t)std::max((long)RES_SPLIT * wrows, part_rows(rows)) * m->cfg.d_model;
 }
 
 int ensure_ws(dllm_model* m, int rows_needed) {
@@ -564,7 +572,7 @@ template <int WT, bool XF32>
 int residual_proj(dllm_model* m, Workspace& w, const PackedW& W, const void* X, const float* gnext, int M, int Mc,
                   int MT, int gy, hipStream_t s, bool sel = false, const uint8_t* need = nullptr, int n_sel = 0) {
     const int d = m->cfg.d_model;
-    const Decomp dc = decomp(G_RES, WT, W, M, MT, gy, w.part_floats);
+    const Decomp dc = decomp(G_RES, WT, W, M, MT, gy, d);
     const int KS = dc.ks;
     if ((size_t)KS * Mc * d > w.part_floats) return fail(DLLM_E_INVAL, "internal: split-K buffer too small");
     GemmArgs g{W.w, W.scale, X, W.KCw, W.KCw * WTraits<WT>::XPER, W.n_tiles};
@@ -651,7 +659,7 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
     // folds.  Models small enough for one slice fold it like the O projection, which saves
     // the reduction's launch (two fp32 layers of d 256: 4.7 of ~50 us per layer).
     const bool fuse_down =
-        fused && decomp(G_RES, WT, m->layers[0].down, a.M, MT, gy, w.part_floats).small;
+        fused && decomp(G_RES, WT, m->layers[0].down, a.M, MT, gy, d).small;
     const bool lm_sel_last = a.lm && a.sel;
     auto nssq_qkv = [&](int l) { return l == 0 ? 1 : m->layers[l - 1].down.n_tiles; };
 
@@ -682,7 +690,7 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
             if (fused && (l == 0 || fuse_down)) fold_norm(g, m, w, nssq_qkv(l));
             EpiQKV<XF32> e{d, m->dkv, Dh, a.M, a.pos_base, a.pos, m->rope, (AT*)w.q, q_plane, Kc, Vt, kv->Cs};
             ProbeScope ps(m, DLLM_K_QKV, s);
-            if ((rc = launch_gemm<WT, G_QKV>(decomp(G_QKV, WT, L.qkv, a.M, MT, gy, w.part_floats), a.M, MT, g, e, gy, s,
+            if ((rc = launch_gemm<WT, G_QKV>(decomp(G_QKV, WT, L.qkv, a.M, MT, gy, d), a.M, MT, g, e, gy, s,
                                              w.part, w.part_floats)))
                 return rc;
         }
@@ -753,7 +761,7 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
             if (fused) fold_norm(g, m, w, L.o.n_tiles);
             EpiSwiGLU<XF32> e{w.af, m->KCx_f};
             ProbeScope ps(m, DLLM_K_GATEUP, s);
-            if ((rc = launch_gemm<WT, G_GU>(decomp(G_GU, WT, L.gu, a.M, MT, gy, 0), a.M, MT, g, e, gy, s)))
+            if ((rc = launch_gemm<WT, G_GU>(decomp(G_GU, WT, L.gu, a.M, MT, gy, d), a.M, MT, g, e, gy, s)))
                 return rc;
         }
         // down projection + residual (+ next norm operand)
@@ -784,7 +792,7 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
         GemmArgs g{m->lm.w, m->lm.scale, w.xg, m->lm.KCw, m->lm.KCw * WTraits<WT>::XPER, m->lm.n_tiles};
         g.qs = m->lm.qs;
         if (fuse_down) fold_norm(g, m, w, m->layers[c.n_layers - 1].down.n_tiles);
-        const Decomp dc = decomp(G_LM, WT, m->lm, Ml, MTl, gyl, 0);
+        const Decomp dc = decomp(G_LM, WT, m->lm, Ml, MTl, gyl, d);
         const int gx = row_groups(dc, m->lm.n_tiles);
         if (gx > m->n_lm_wg) return fail(DLLM_E_INVAL, "internal: LM-head partials exceed their buffer");
         if (Ml > 0) {

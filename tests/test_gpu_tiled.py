@@ -8,7 +8,7 @@ import pytest
 
 import oracle
 import synth
-from gpu_util import assert_logits_close, build_pair, dev_i32, gpu_logits
+from gpu_util import assert_logits_close, build_pair, dev_i32, gpu_logits, gpu_step
 
 pytestmark = pytest.mark.gpu
 
@@ -114,4 +114,33 @@ def test_two_tile_prompt_rows(n):
     assert np.abs(K[1][:, :n] - rk).max() <= _bound(rk)
     assert np.abs(Vt[1][:, :, :n].transpose(0, 2, 1) - rv).max() <= _bound(rv)
     kv.close()
+    model.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "w8", "q4"])
+def test_results_do_not_depend_on_earlier_calls(dtype):
+    """A 100-row prompt and a 96-row window on a new model, and again after a 600-row prompt has
+    grown its workspace: the same bits in the cache, the ids and the confidences."""
+    import torch
+    import paper_2606_13740_amd as dl
+
+    shape = RAGGED
+    model, _, _ = build_pair(shape, dtype, max_window=96, max_pos=640, oracle_too=False)
+    tok, mask = synth.window(shape, 96, range(30, 96))
+
+    def once():
+        kv = dl.KVCache(model, 196)
+        dl.dllm_prefill(model.handle, kv.handle, dev_i32(synth.prompt_ids(shape, 100)), 100)
+        ids, conf = gpu_step(model, kv, tok, mask)
+        out = kv.buf.cpu().numpy(), ids, conf
+        kv.close()
+        return out
+
+    before = once()
+    kv = dl.KVCache(model, 600)
+    dl.dllm_prefill(model.handle, kv.handle, dev_i32(synth.prompt_ids(shape, 600)), 600)
+    torch.cuda.synchronize()
+    kv.close()
+    for a, b in zip(before, once()):
+        np.testing.assert_array_equal(a, b)
     model.close()

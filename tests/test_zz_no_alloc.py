@@ -56,6 +56,21 @@ def test_noalloc_step_equals_step_two_calls_shrinking(dtype):
     model.close()
 
 
+@pytest.mark.parametrize("max_window", [128, 256])
+@pytest.mark.parametrize("dtype", ["bf16", "w8", "q4"])
+def test_noalloc_step_equals_step_past_64_rows(dtype, max_window):
+    """96 rows: the scratch holds fewer split-K partials than a model's workspace of larger
+    windows, and the K slices are the same all the same (bit for bit)."""
+    sh = synth.SMALL_BF16
+    print(f"case: no-alloc step past 64 rows, {dtype}, max_window {max_window}", flush=True)
+    model, _, _ = build_pair(sh, dtype, max_window=max_window, max_pos=512, oracle_too=False)
+    kv = dl.KVCache(model, 64 + 96)
+    dl.dllm_prefill(model.handle, kv.handle, dev_i32(synth.prompt_ids(sh, 64)), 64)
+    _check_pair(model, kv, 96, list(range(8, 96)))
+    kv.close()
+    model.close()
+
+
 def test_noalloc_step_8b_width():
     sh = synth.LLADA_8B.with_layers(2)
     print("case: no-alloc step, LLaDA-8B widths, 2 layers, prefix 512", flush=True)
