@@ -159,14 +159,17 @@ attn_f16_kernel(AttnArgs a) {
     int lim[QT];
 #pragma unroll
     for (int q = 0; q < QT; ++q) {
+        // Rows past the last real one repeat it: q holds what earlier calls left there, and
+        // the rescale below is decided over all 16 rows of a tile, so a stale row would
+        // reach the last bits of the real ones.
+        const int rq = min(row + 16 * q, a.M - 1);
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            // a last group may reach past the padded rows: those lanes read its last row
-            const uint16_t* src = qp + (size_t)min(row + 16 * q, a.rows - 1) * ld + h * DH + 32 * c + 8 * g;
+            const uint16_t* src = qp + (size_t)rq * ld + h * DH + 32 * c + 8 * g;
             qf[q][c][0] = ldg16(src);
             qf[q][c][1] = ldg16(src + a.q_plane);
         }
-        lim[q] = (a.lim != nullptr && row + 16 * q < a.M) ? a.lim[row + 16 * q] : a.T;
+        lim[q] = a.lim != nullptr ? a.lim[rq] : a.T;
     }
 
     // Ring of NB buffers: the first NB - 1 blocks are staged here (after the Q loads, so

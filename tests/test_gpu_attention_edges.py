@@ -14,13 +14,15 @@
   cache's rounding then moves the scores by ~2^10 times more too (7e-2 off the exact
   oracle at 64 rows, the same as a softmax rescaled on every block), so these cases
   compare with the oracle storing its K/V in fp16 as well.
+- Windows that do not fill their last query tile, on such scores: the rows past the
+  window must not reach it, whatever earlier calls left there.
 """
 import numpy as np
 import pytest
 
 import oracle
 import synth
-from gpu_util import GLOBALS, assert_ids_match_where_decided, assert_logits_close, dev_i32, gpu_logits, tol
+from gpu_util import GLOBALS, assert_ids_match_where_decided, assert_logits_close, dev_i32, dev_u8, gpu_logits, tol
 
 pytestmark = pytest.mark.gpu
 
@@ -102,3 +104,31 @@ def test_wide_score_range_matches_oracle(P, W):
     print(f"  argmax decided on {frac:.0%} of rows", flush=True)
     np.testing.assert_allclose(conf, ref.conf, rtol=0.2)
     model.close()
+
+
+@pytest.mark.parametrize("W", [20, 39])
+def test_partial_query_tile_does_not_see_earlier_calls(W):
+    """A window of 4 or 7 rows past a whole tile in the shared scratch of the no-allocation step,
+    before and after a 64-row window of a model with ~2^10 times the scores has left its Q
+    rows there: the same bits.  (A row of the tile whose scores grow moves the softmax
+    reference of all 16.)"""
+    wide = _model(_scale_qk(synth.all_weights(SH, "bf16"), 5))
+    model = _model(_scale_qk(synth.all_weights(SH, "bf16"), 1))
+    P = 300
+    kv, kvw = dl.KVCache(model, P + W), dl.KVCache(wide, P + 64)
+    for m, c in ((model, kv), (wide, kvw)):
+        dl.dllm_prefill(m.handle, c.handle, dev_i32(synth.prompt_ids(SH, P)), P)
+
+    def step(m, c, n, masked):
+        tok, mask = synth.window(SH, n, masked)
+        ids, conf = torch.empty(n, dtype=torch.int32, device="cuda"), torch.empty(n, device="cuda")
+        dl.dllm_denoise_step_noalloc(m.handle, c.handle, dev_i32(tok), dev_u8(mask), n, ids, conf)
+        torch.cuda.synchronize()
+        return ids.cpu().numpy(), conf.cpu().numpy(), c.buf.cpu().numpy()
+
+    first = step(model, kv, W, range(W // 4, W))
+    step(wide, kvw, 64, [])
+    for a, b in zip(first, step(model, kv, W, range(W // 4, W))):
+        np.testing.assert_array_equal(a, b)
+    for h in (kv, kvw, model, wide):
+        h.close()
