@@ -252,6 +252,14 @@ constexpr int template_fw(GemmKind k, int wt, int mt) {
 }
 int template_nwn(GemmKind k) { return k == G_LM ? 4 : 1; }
 
+// A narrower Q4_0 template for groups of few row tiles past 2 token tiles: the full one runs
+// every slot's MFMAs, and gate/up's 6 tiles x 4 token tiles take all 256 registers and spill 12
+// in the loop.  us per launch, 6 against 3 tiles: gate/up of d 1024 at 48 and 64 rows 14.3 and
+// 11.3, 19.1 and 13.2; of d 2048 19.2 and 14.9, 28.3 and 17.6; 3 against 2 tiles: QKV of d 2048
+// at 64 rows 14.7 and 13.1.  Groups of 4-6 tiles (LLaDA-8B) stay: 50.7 at 64 rows, 49.7 with
+// 3 tiles in two rounds, but 31.1 and 41.4 at 48.
+constexpr int q4_narrow(GemmKind k) { return k == G_QKV ? 2 : 3; }
+
 // W: the packed operand of M token rows, computed as gy blocks of MT tiles (Mc rows) by
 // the streaming layouts.  d: d_model.
 Decomp decomp(GemmKind k, int wt, const PackedW& W, int M, int MT, int gy, int d) {
@@ -358,6 +366,14 @@ int launch_gemm(const Decomp& dc, int M, int MT, const GemmArgs& g0, const Epi& 
         }
     }
     if (dc.small) return launch_gemm_mt<WT, -1, 1, SMALL_WAVES>(MT, g, epi, n_tiles, dc.ks, gy, s);
+    if constexpr (WT == WT_Q4 && KIND != G_LM) {
+        if (MT >= 3 && g.tpg <= q4_narrow(KIND)) {
+            const int ks = KIND == G_RES ? dc.ks : 1;
+            if (MT == 3) launch_gemm_inst<WT, q4_narrow(KIND), 1, 8, 3>(g, epi, n_tiles, ks, gy, s);
+            else launch_gemm_inst<WT, q4_narrow(KIND), 1, 8, 4>(g, epi, n_tiles, ks, gy, s);
+            return DLLM_OK;
+        }
+    }
     if constexpr (KIND == G_GU && WT == WT_BF16) {
         if (g.tpg > template_fw(G_GU, WT, MT)) {
             if (g.tpg > GU_WIDE_TILES || MT > 2) return fail(DLLM_E_INVAL, "internal: gate/up tiles outside the templates");

@@ -117,3 +117,24 @@ def test_q4_cache_equals_block_causal_recompute(q4pair):
     np.testing.assert_allclose(Kg[:, :, :n].cpu().numpy(), np.transpose(K, (0, 2, 1, 3)), atol=3e-2, rtol=3e-2)
     np.testing.assert_allclose(Vt[:, :, :, :n].cpu().numpy(), np.transpose(V, (0, 2, 3, 1)), atol=3e-2, rtol=3e-2)
     kv.close()
+
+
+@pytest.mark.parametrize("W", [33, 48, 64])
+def test_q4_narrow_groups_match_oracle(W):
+    """Widths whose row groups hold fewer tiles than the full templates past 32 rows: QKV 2
+    (320 row tiles in 160 groups), down 3 (192 in 64, K in slices), gate/up 1-3."""
+    sh = synth.Shape(n_layers=2, d_model=3072, n_heads=24, head_dim=128, d_ff=2064, vocab=500, mask_id=499,
+                     n_kv_heads=8)
+    print(f"case: Q4_0 narrow groups, window {W}", flush=True)
+    model, om, _ = build_pair(sh, "q4", max_window=64, max_pos=128)
+    kv, okv = dl.KVCache(model, 40 + W), oracle.OracleKV(sh, 40 + W)
+    prompt = synth.prompt_ids(sh, 40)
+    dl.dllm_prefill(model.handle, kv.handle, dev_i32(prompt), 40)
+    oracle.prefill(om, okv, prompt)
+    tok, mask = synth.window(sh, W, range(W // 4, W))
+    logits, ids, _ = gpu_logits(model, kv, tok, mask)
+    ref = oracle.denoise_step(om, okv, tok, mask)
+    err = assert_logits_close(logits, ref.logits, tol("q4"))
+    assert_ids_match_where_decided(ids, ref.logits, err)
+    kv.close()
+    model.close()
