@@ -142,6 +142,9 @@ namespace {
 
 // Waves of a small model's one-tile workgroups, K over them: latency-bound, so as many as
 // still have a chunk each (two fp32 layers of d 256, 32 rows: 91 us per step with 8, 99 with 4).
+// Half of them past 64 rows, where a CU takes several workgroups (bf16 gate/up of d 256 at 144
+// rows 6.6 us with 4 and 10.8 with 8; int8 O and down of d 1024 at 128 rows 9.6 and 10.5, 13.0
+// and 14.1), except Q4_0 in one round (10.1 and 8.9, 16.2 and 14.1).
 constexpr int SMALL_WAVES = 8;
 
 enum GemmKind { G_QKV = 0, G_RES = 1, G_GU = 2, G_LM = 3 };
@@ -186,13 +189,10 @@ constexpr int N_CU = 256;
 // stages where the 6-tile template runs 3, so the LLaDA-8B widths keep the 6-tile one.
 constexpr int GU_WIDE_TILES = 10;
 
-// Every GEMM over more than 64 token rows (prompts, wide windows) except the LM head and
-// those of fp32 models runs the LDS-tiled kernel: each weight and activation chunk is
-// fetched once per workgroup and shared by its waves, where the streaming layouts re-read
-// the activations per row group and the weights per 64 rows.  int8 from 129 to 192 rows
-// stays with the streaming layouts: those rows are three of their 64-row blocks but two
-// half-filled 128-row tiles, whose widening is not hidden (three layers of the LLaDA-8B
-// shape at 144 rows: 789 against 842 us; at 128 rows 626 and 629, at 208 929 and 864).
+// GEMMs over more than 64 token rows (prompts, wide windows), except the LM head, those of
+// fp32 models and where streaming_wins, run the LDS-tiled kernel: each weight and activation
+// chunk is fetched once per workgroup and shared by its waves, where the streaming layouts
+// re-read the activations per row group and the weights per 64 rows.
 //
 // Which rt x tt tiles a workgroup takes, and how many K slices, is the cheapest of the
 // shapes below under a model of the launch: rounds of workgroups over the chip, each of
@@ -260,15 +260,10 @@ int template_nwn(GemmKind k) { return k == G_LM ? 4 : 1; }
 // 3 tiles in two rounds, but 31.1 and 41.4 at 48.
 constexpr int q4_narrow(GemmKind k) { return k == G_QKV ? 2 : 3; }
 
-// W: the packed operand of M token rows, computed as gy blocks of MT tiles (Mc rows) by
-// the streaming layouts.  d: d_model.
-Decomp decomp(GemmKind k, int wt, const PackedW& W, int M, int MT, int gy, int d) {
-    const int n_tiles = W.n_tiles, Mc = gy * MT * 16;
-    if (wt != WT_F32 && k != G_LM && M > 64 && !(wt == WT_I8 && M > 128 && M <= 192)) {
-        const int steps = W.KCw * (kc_of(wt) / 32);
-        const TiledPlan p = tiled_plan(k, n_tiles, steps, ceil_div(M, 16), Mc, (size_t)part_rows(Mc) * d);
-        return Decomp{false, 0, p.ks, p.rt, p.tt};
-    }
+// The streaming layouts' row groups and K slices of n_tiles row tiles for gy blocks of MT
+// token tiles (Mc rows).
+Decomp stream_decomp(GemmKind k, int wt, int n_tiles, int MT, int gy) {
+    const int Mc = gy * MT * 16;
     const int min_tiles = (k == G_QKV || k == G_RES) ? 128 : (k == G_GU ? 256 : 512);
     if (n_tiles < min_tiles) return Decomp{true, 1, 1};
     const int fw = template_fw(k, wt, MT), nwn = template_nwn(k);
@@ -289,6 +284,46 @@ Decomp decomp(GemmKind k, int wt, const PackedW& W, int M, int MT, int gy, int d
         }
     }
     return best;
+}
+
+// Past 64 rows: whether the streaming layouts (sd, gy blocks of 64 rows) take the GEMM from
+// the tiled kernel.  They win while their workgroups fit about one round of the chip and K
+// is short: a tiled workgroup's start, its K slices and their finish then cost more than
+// re-reading the weights per 64 rows, and int8 and Q4_0 weights are widened by four waves
+// each there.  us per launch with its finish, streaming against tiled, in order of the lines:
+//   one-tile groups (narrow models): d 256, 65 rows: QKV bf16 6.7 and 9.0, int8 6.0 and 10.8,
+//     Q4_0 5.0 and 9.9; gate/up 6.4 and 7.5, 5.8 and 9.9, 4.5 and 9.2; O bf16 8.6 and 7.0,
+//     int8 7.8 and 8.8, Q4_0 7.0 and 7.8; d 1536 down, 192 rows, int8 24.8 and 18.9.  Whole
+//     prompts of four layers of d 256, streaming against tiled: bf16 384 rows 217 and 215,
+//     int8 768 rows 312 and 309, Q4_0 1500 rows 388 and 386
+//   O of 129-256 rows, int8 / Q4_0: LLaDA-8B 208 rows 27.7 and 30.6, 29.7 and 31.9; two
+//     rounds: 41.9 and 30.4; down of d 2048, 208 rows, int8: 30.0 and 24.8
+//   int8 gate/up of three full rounds of full groups (LLaDA-8B, 129-192 rows): 82.6 and
+//     95.6; ragged rounds (Dream-7B): 141 and 124
+//   QKV and gate/up: bf16 d 2048 QKV, 128 rows 14.9 and 19.1, d 3072 23.2 and 20.1; gate/up
+//     d 1536 15.8 and 20.5, d 2048 25.3 and 23.8; int8 Dream-7B QKV (3584 columns) 19.9 and
+//     25.9, LLaDA-8B (two rounds) 41.5 and 38.3
+bool streaming_wins(GemmKind k, int wt, const Decomp& sd, int n_tiles, int steps, int M, int gy) {
+    const long wgs = (long)ceil_div(n_tiles, sd.tpg) * gy;
+    if (sd.small) {
+        if (wt == WT_BF16) return k != G_RES && wgs <= 2 * N_CU;
+        return wgs <= (wt == WT_I8 ? 768 : 1376) && wgs * steps <= 28000;
+    }
+    if (k == G_RES) return wt != WT_BF16 && M > 128 && M <= 256 && wgs <= N_CU && steps <= 128;
+    if (wt == WT_I8 && k == G_GU && M > 128 && M <= 192 && sd.tpg == template_fw(G_GU, wt, 4) && wgs % N_CU == 0)
+        return true;
+    return wgs <= N_CU && steps <= (wt != WT_BF16 ? 112 : k == G_QKV ? 64 : 48);
+}
+
+// W: the packed operand of M token rows, computed as gy blocks of MT tiles by the streaming
+// layouts.  d: d_model.
+Decomp decomp(GemmKind k, int wt, const PackedW& W, int M, int MT, int gy, int d) {
+    const Decomp sd = stream_decomp(k, wt, W.n_tiles, MT, gy);
+    if (wt == WT_F32 || k == G_LM || M <= 64) return sd;
+    const int steps = W.KCw * (kc_of(wt) / 32), Mc = gy * MT * 16;
+    if (streaming_wins(k, wt, sd, W.n_tiles, steps, M, gy)) return sd;
+    const TiledPlan p = tiled_plan(k, W.n_tiles, steps, ceil_div(M, 16), Mc, (size_t)part_rows(Mc) * d);
+    return Decomp{false, 0, p.ks, p.rt, p.tt};
 }
 
 template <int WT, int FW, int NWn, int NWk, int MT, class Epi>
@@ -365,7 +400,14 @@ int launch_gemm(const Decomp& dc, int M, int MT, const GemmArgs& g0, const Epi& 
             return launch_tiled<WT>(dc, g, epi, m_tiles, s);
         }
     }
-    if (dc.small) return launch_gemm_mt<WT, -1, 1, SMALL_WAVES>(MT, g, epi, n_tiles, dc.ks, gy, s);
+    if (dc.small) {
+        if (gy > 1 && (WT != WT_Q4 || n_tiles * gy > N_CU)) {
+            if (MT != 4) return fail(DLLM_E_INVAL, "internal: token blocks of 64 rows expected");
+            launch_gemm_inst<WT, 1, 1, SMALL_WAVES / 2, 4>(g, epi, n_tiles, dc.ks, gy, s);
+            return DLLM_OK;
+        }
+        return launch_gemm_mt<WT, -1, 1, SMALL_WAVES>(MT, g, epi, n_tiles, dc.ks, gy, s);
+    }
     if constexpr (WT == WT_Q4 && KIND != G_LM) {
         if (MT >= 3 && g.tpg <= q4_narrow(KIND)) {
             const int ks = KIND == G_RES ? dc.ks : 1;
