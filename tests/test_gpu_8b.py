@@ -86,10 +86,12 @@ def _run(shape, dtype, P, W, masked, cap_extra=0, sls=False):
 
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("dtype,P,W", [("bf16", 512, 32), ("bf16", 512, 48), ("bf16", 1024, 64), ("w8", 512, 64),
-                                       ("q4", 512, 32), ("q4", 512, 48), ("q4", 512, 64), ("bf16", 440, 32)])
+                                       ("q4", 512, 32), ("q4", 512, 48), ("q4", 512, 64), ("bf16", 440, 32),
+                                       ("bf16", 200, 32), ("w8", 200, 32), ("q4", 257, 32)])
 def test_8b_width_two_layers(dtype, P, W):
-    """The bench's launches at the 8B widths; the 440-token prompt (448 rows) takes the
-    prompt's split-K QKV with a ragged second token group (12 of 16 token tiles)."""
+    """The bench's launches at the 8B widths, and prompts that fill the tiled GEMM's last tokens
+    only in part: 440 (QKV in one K slice, 28 of 32 token tiles), 200 (QKV in two slices,
+    13 of 16), 257 (Q4_0 down in 16 x 16 tiles and eight slices, 17 of 32)."""
     masked = list(range(8, 32)) if W == 32 else list(range(24, W))
     _run(BIG.with_layers(2), dtype, P, W, masked)
 
@@ -97,10 +99,10 @@ def test_8b_width_two_layers(dtype, P, W):
 @pytest.mark.timeout(900)
 def test_8b_width_long_prefix_int8_spec_window():
     """The long-prefix int8 speculative launch configuration at the 8B widths: int8
-    weights, a 64-row window, and a prefix long enough that the attention's key
-    splits hit their cap (2048 keys: 66 blocks in 14 splits; the 4096-key workload
-    takes 15 splits through the same code).  One layer: the oracle's prefill is the
-    cost."""
+    weights, a 64-row window, and a prefix whose 66 blocks of 32 keys the attention
+    cuts into 8 splits, one workgroup per CU over the 32 heads (the 4096-key workload: 130
+    blocks in 8 splits, with a third staging buffer).  One layer: the oracle's prefill is
+    the cost."""
     _run(BIG.with_layers(1), "w8", 2048, 64, list(range(0, 64)))
 
 
@@ -130,7 +132,7 @@ def test_8b_full_depth_int8_spec_window_sls():
 @pytest.mark.timeout(900)
 def test_8b_width_int8_prefix_4096_spec_window():
     """The long-prefix int8 workload's launches at its own prefix: 4096 keys + the
-    64-row window = 130 key blocks in 15 attention splits, through the selective-logits
+    64-row window = 130 key blocks in 8 attention splits, through the selective-logits
     call the benchmark makes.  Two layers (the oracle's 4096-token prefill is the cost)."""
     _run(BIG.with_layers(2), "w8", 4096, 64, list(range(0, 64)), sls=True)
 

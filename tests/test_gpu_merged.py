@@ -94,6 +94,46 @@ def test_merged_matches_sequential_oracle(case):
     model.close()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "w8", "q4"])
+@pytest.mark.parametrize("W,max_window", [(61, 128), (161, 256)])
+def test_merged_past_64_rows_matches_oracle(dtype, W, max_window):
+    """8 refresh + 32 appended + 61 or 161 window rows over 480 keys: explicit positions and per-row
+    key limits past 64 rows, in the streaming layouts (101 rows) and the tiled kernel with
+    QKV in K slices (201), over several key splits of which the refreshed rows near the start
+    see only the first.  K, V and the confidences are off by a few fp16 roundings of the cache
+    (2^-11) per layer; a confidence's relative error is at most twice a logit's absolute one."""
+    sh = synth.Shape(n_layers=2, d_model=1152, n_heads=9, head_dim=128, d_ff=1504, vocab=500, mask_id=499)
+    B, P, n_ref = sh.block, 480, 8
+    cap = P + B + W
+    print(f"case: merged past 64 rows, {dtype}: {n_ref} refresh + {B} append + {W} window rows", flush=True)
+    model, om, _ = build_pair(sh, dtype, max_window=max_window, max_pos=cap)
+    kv, okv = dl.KVCache(model, cap), oracle.OracleKV(sh, cap)
+    prompt = synth.prompt_ids(sh, P)
+    dl.dllm_prefill(model.handle, kv.handle, dev_i32(prompt), P)
+    oracle.prefill(om, okv, prompt)
+    ref_pos = np.array([3, 31, 32, 70, 200, 333, 448, P - 1], np.int32)
+    ref_new = synth.uniform_ids(83, 1, n_ref, sh.mask_id)
+    blk = synth.uniform_ids(73, 1, B, sh.mask_id)
+    tok, mask = synth.window(sh, W, range(W // 4, W))
+    ids, conf, rids, rconf = _merged(model, kv, ref_pos, ref_new, blk, tok, mask)
+    r_ids, r_conf, r_logits = oracle.refresh(om, okv, ref_pos, ref_new, lm_head=True)
+    oracle.append_block(om, okv, blk)
+    so = oracle.denoise_step(om, okv, tok, mask)
+    (Kg, Vg), (Kr, Vr) = _cache(kv, cap), _oracle_cache(okv, cap)
+
+    def bound(ref):
+        return 4 * 2.0 ** -11 * np.abs(ref[np.isfinite(ref)]).max()
+
+    assert np.abs(Kg - Kr).max() <= bound(Kr) and np.abs(Vg - Vr).max() <= bound(Vr)
+    lb = max(bound(so.logits), bound(r_logits))
+    np.testing.assert_allclose(conf, so.conf, rtol=2 * lb)
+    np.testing.assert_allclose(rconf, r_conf, rtol=2 * lb)
+    assert_ids_match_where_decided(ids, so.logits, lb)
+    assert_ids_match_where_decided(rids, r_logits, lb)
+    kv.close()
+    model.close()
+
+
 def test_merged_single_groups_equal_the_single_calls():
     """Each group alone through dllm_step_merged equals the dedicated entry point (fp32 model)."""
     sh = synth.TINY
