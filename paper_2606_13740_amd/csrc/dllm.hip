@@ -775,11 +775,14 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
                 const int nqg = ceil_div(Mc, 16 * QG * (two ? 2 : 1));
                 // Key splits across workgroups, merged by attn_combine, up to one workgroup
                 // per CU (64 rows over 4160 keys, 32 heads: 8 splits 24.3 us, 12 splits 24.9,
-                // 6 splits 26.3; 256 rows over 1700: 2 splits 28.2, 1 split 41), while the
+                // 6 splits 26.3; 256 rows over 1700: 2 splits 28.2, 1 split 41), two where a
+                // workgroup is a single wave (16 rows, three layers: LLaDA-8B over 4016 keys
+                // 345 -> 338 us, Dream-7B's 28 heads over 8016 393 -> 366), while the
                 // partials' workspace holds the rows, and of at least 3 blocks (32 rows over
                 // 544 keys: 6 splits of 3 blocks 9.0, 9 of 2 9.6, 5 of 4 9.3)
                 const int nblk = ceil_div(a.T, 32);
-                int nsplit = Mc <= w.wrows ? std::min(std::max(1, N_CU / (H * nqg)), MAX_SPLIT) : 1;
+                const int max_wgs = QG == 1 ? 2 * N_CU : N_CU;
+                int nsplit = Mc <= w.wrows ? std::min(std::max(1, max_wgs / (H * nqg)), MAX_SPLIT) : 1;
                 at.bps = std::max(ceil_div(nblk, nsplit), 3);
                 at.nsplit = ceil_div(nblk, at.bps);
                 dim3 grid(at.nsplit * H * nqg);

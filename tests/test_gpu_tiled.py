@@ -79,7 +79,7 @@ def test_wide_window(dtype, W):
 def test_long_prompt_attention_head_64():
     """32 heads of 64: a prompt long enough for two query tiles per wave whose last row group is
     half empty (its second layer's K/V depend on them), then steps whose key splits are long
-    enough for three staging buffers."""
+    enough for three staging buffers, or (9 rows) two to a CU."""
     import paper_2606_13740_amd as dl
 
     shape = synth.Shape(n_layers=2, d_model=2048, n_heads=32, head_dim=64, d_ff=256, vocab=500, mask_id=499)
@@ -90,7 +90,7 @@ def test_long_prompt_attention_head_64():
     dl.dllm_prefill(model.handle, kv.handle, dev_i32(prompt), n)
     okv = oracle.OracleKV(shape, n + 64)
     oracle.prefill(om, okv, prompt)
-    for W in (17, 33, 64):
+    for W in (9, 17, 33, 64):
         tok, mask = synth.window(shape, W, range(4, W))
         got, _, _ = gpu_logits(model, kv, tok, mask)
         ref = oracle.denoise_step(om, okv, tok, mask)
