@@ -298,11 +298,15 @@ Decomp stream_decomp(GemmKind k, int wt, int n_tiles, int MT, int gy) {
 //     int8 768 rows 312 and 309, Q4_0 1500 rows 388 and 386
 //   O of 129-256 rows, int8 / Q4_0: LLaDA-8B 208 rows 27.7 and 30.6, 29.7 and 31.9; two
 //     rounds: 41.9 and 30.4; down of d 2048, 208 rows, int8: 30.0 and 24.8
-//   int8 gate/up of three full rounds of full groups (LLaDA-8B, 129-192 rows): 82.6 and
-//     95.6; ragged rounds (Dream-7B): 141 and 124
 //   QKV and gate/up: bf16 d 2048 QKV, 128 rows 14.9 and 19.1, d 3072 23.2 and 20.1; gate/up
-//     d 1536 15.8 and 20.5, d 2048 25.3 and 23.8; int8 Dream-7B QKV (3584 columns) 19.9 and
-//     25.9, LLaDA-8B (two rounds) 41.5 and 38.3
+//     d 1536 15.8 and 20.5, d 2048 25.3 and 23.8
+//   int8 gate/up of 129-192 rows, which half fill two token groups of the tiled kernel, in up
+//     to three rounds of full groups: LLaDA-8B 82.6 and 95.6, d 2560 40.4 and 46.8; rounds
+//     filled less (d 2048: 0.69) 38.5 and 34.3; five rounds (Dream-7B) 141 and 124
+//   int8 / Q4_0 QKV in two rounds: d 2560 144 rows 28.9 and 32.0, 29.3 and 34.5; Q4_0 96 rows
+//     24.8 and 30.3 (int8 27.5 and 27.2); d 2048 256 rows 25.7 and 26.7, 26.6 and 29.3, d 3072
+//     37.0 and 34.2, 36.9 and 35.0
+//   else one round: int8 Dream-7B QKV (3584 columns) 19.9 and 25.9, LLaDA-8B (4096) 41.5 and 38.3
 bool streaming_wins(GemmKind k, int wt, const Decomp& sd, int n_tiles, int steps, int M, int gy) {
     const long wgs = (long)ceil_div(n_tiles, sd.tpg) * gy;
     if (sd.small) {
@@ -310,9 +314,14 @@ bool streaming_wins(GemmKind k, int wt, const Decomp& sd, int n_tiles, int steps
         return wgs <= (wt == WT_I8 ? 768 : 1376) && wgs * steps <= 28000;
     }
     if (k == G_RES) return wt != WT_BF16 && M > 128 && M <= 256 && wgs <= N_CU && steps <= 128;
-    if (wt == WT_I8 && k == G_GU && M > 128 && M <= 192 && sd.tpg == template_fw(G_GU, wt, 4) && wgs % N_CU == 0)
-        return true;
-    return wgs <= N_CU && steps <= (wt != WT_BF16 ? 112 : k == G_QKV ? 64 : 48);
+    if (wt == WT_BF16) return wgs <= N_CU && steps <= (k == G_QKV ? 64 : 48);
+    const int rounds = ceil_div(wgs, N_CU);
+    const bool half_tiles = M > 128 && M <= 192;
+    if (k == G_GU && wt == WT_I8 && half_tiles && sd.tpg == template_fw(G_GU, wt, 4) && rounds <= 3)
+        return wgs >= (long)(0.8 * N_CU * rounds);
+    if (k == G_QKV && rounds == 2 && (half_tiles || (wt == WT_Q4 && M <= 192) || (M <= 256 && steps <= 64)))
+        return steps <= 112;
+    return rounds == 1 && steps <= 112;
 }
 
 // W: the packed operand of M token rows, computed as gy blocks of MT tiles by the streaming
