@@ -723,10 +723,12 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
     // normalised operand) where it splits: over the whole K range each of its workgroups
     // would read the whole 12288-wide activation (4x the L2 traffic of 4 split-K slices).
     // QKV then reads a normalised operand, except after the embedding (layer 0), which
-    // folds.  Models small enough for one slice fold it like the O projection, which saves
-    // the reduction's launch (two fp32 layers of d 256: 4.7 of ~50 us per layer).
+    // folds.  Models small enough for one slice fold it like the O projection up to 48 rows,
+    // which saves the reduction's launch (two fp32 layers of d 256: 4.7 of ~50 us per layer;
+    // four bf16 layers of d 512, 16 rows 145 against 150 us; 64 rows 197 against 193: every
+    // QKV workgroup sums the partials of all rows).
     const bool fuse_down =
-        fused && decomp(G_RES, WT, m->layers[0].down, a.M, MT, gy, d).small;
+        fused && MT <= 3 && decomp(G_RES, WT, m->layers[0].down, a.M, MT, gy, d).small;
     const bool lm_sel_last = a.lm && a.sel;
     auto nssq_qkv = [&](int l) { return l == 0 ? 1 : m->layers[l - 1].down.n_tiles; };
 
