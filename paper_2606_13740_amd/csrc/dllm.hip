@@ -790,10 +790,14 @@ int forward_t(dllm_model* m, dllm_kv* kv, const FwdArgs& a, hipStream_t s) {
                 // workgroup is a single wave (16 rows, three layers: LLaDA-8B over 4016 keys
                 // 345 -> 338 us, Dream-7B's 28 heads over 8016 393 -> 366), while the
                 // partials' workspace holds the rows, and of at least 3 blocks (32 rows over
-                // 544 keys: 6 splits of 3 blocks 9.0, 9 of 2 9.6, 5 of 4 9.3)
+                // 544 keys: 6 splits of 3 blocks 9.0, 9 of 2 9.6, 5 of 4 9.3).  Six blocks of
+                // 33 or more rows stay whole, as the merge's launch costs more (three layers
+                // of 64 rows over 134 keys: LLaDA-8B 439 us against 443, Dream-7B 531 and 537;
+                // four of 16 heads of 64, int8, 104 keys: 237 and 245)
                 const int nblk = ceil_div(a.T, 32);
                 const int max_wgs = QG == 1 ? 2 * N_CU : N_CU;
                 int nsplit = Mc <= w.wrows ? std::min(std::max(1, max_wgs / (H * nqg)), MAX_SPLIT) : 1;
+                if (QG >= 3 && nblk <= 6) nsplit = 1;
                 at.bps = std::max(ceil_div(nblk, nsplit), 3);
                 at.nsplit = ceil_div(nblk, at.bps);
                 dim3 grid(at.nsplit * H * nqg);
