@@ -87,14 +87,16 @@ attn_f16_kernel(AttnArgs a) {
     const int lane = threadIdx.x & 63, qw = QG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, g = lane >> 4;
     // 1-D grid over (head h, query group z, split) items, in that order.  The dispatcher
-    // deals consecutive workgroups to the 8 XCDs in turn; when the items divide into
-    // 8 equal shares, XCD x takes the x-th share, so the query groups and splits of a
+    // deals consecutive workgroups to the 8 XCDs in turn; XCD x takes the x-th of 8 shares
+    // (the first nitems mod 8 hold one item more), so the query groups and splits of a
     // head (which read the same K/V, the splits adjacent 64-byte halves of the same
-    // V^T lines) share one L2.
+    // V^T lines) and the heads of a K/V group share one L2.  (Three Dream-7B layers, 28 heads
+    // in 9 splits, 32 rows over 4032 keys: 404 us with the 252 items, which do not divide by
+    // 8, in the dispatcher's order, 401 so; over 8032 keys 431 and 427.)
     const int nitems = (int)gridDim.x;
     const int nqg = nitems / (a.nsplit * a.H);
-    int item = blockIdx.x;
-    if ((nitems & 7) == 0) item = (blockIdx.x & 7) * (nitems >> 3) + (blockIdx.x >> 3);
+    const int xcd = blockIdx.x & 7;
+    const int item = xcd * (nitems >> 3) + min(xcd, nitems & 7) + (int)(blockIdx.x >> 3);
     const int split = item % a.nsplit, z = (item / a.nsplit) % nqg, h = item / (a.nsplit * nqg);
     const int row = z * 16 * QG * QT + 16 * QT * qw + r;     // this lane's first query row (+ 16 per tile)
     const int ld = a.H * DH;
