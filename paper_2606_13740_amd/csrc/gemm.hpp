@@ -250,12 +250,6 @@ gemm_kernel(GemmArgs g, Epi epi) {
         bx = (int)((j / gridDim.z) * 8 + (L & 7));
         bz = (int)(j % gridDim.z);
     }
-    // One token block: an XCD takes neighbouring row groups, whose outputs share 128-byte
-    // lines of x, Q and K (48 or 64 bytes per group), so that its L2 writes whole lines.
-    // Three layers of the LLaDA-8B shape in bf16 at 16 and 32 rows 308.2 -> 306.7 and 337.6
-    // -> 335.4 us, Q4_0 at 16 rows 203.4 -> 201.0; no gain at 4 token tiles (442 -> 445).
-    if (MT <= 3 && gridDim.z == 1 && gridDim.y == 1 && (gridDim.x & 7) == 0)
-        bx = (bx & 7) * (int)(gridDim.x >> 3) + (bx >> 3);
     const int mt0 = bz * MT;
     // K range of this split (32-bit unsigned: KCw * KS is far below 2^32, and a 64-bit
     // division would delay the first weight load by a few hundred scalar instructions)
