@@ -173,9 +173,9 @@ int pick_MT(int M) {
 // layouts above at the LLaDA-8B widths (256 or 247 workgroups) and e.g. 5 tiles
 // per wave group for the Dream-7B LM head (its gate/up takes the 10-tile template
 // below).  Small models (fewer row tiles than the thresholds below) use one tile per
-// 4-wave workgroup.
+// workgroup of SMALL_WAVES waves.
 struct Decomp {
-    bool small;   // 1 tile per workgroup of 4 waves, K over the waves
+    bool small;   // 1 tile per workgroup, K over its waves (SMALL_WAVES)
     int tpg;      // row tiles per wave group
     int ks;       // split-K slices (residual projections)
     int rt = 0, tt = 0;  // > 64 rows: gemm_tiled_kernel with rt x tt tiles per workgroup (tiled_plan)
@@ -201,7 +201,9 @@ constexpr int GU_WIDE_TILES = 10;
 // of 4.2 ns, measured (bf16, one round): a step of 16 x 16 tiles 1.29 us, 12 x 16 1.17,
 // 16 x 8 0.79, 12 x 8 0.67, 8 x 8 0.48 alone on a CU and 0.89 for two (its 80 KiB of LDS
 // let two workgroups share one), 6 x 8 0.52 on all CUs (gate/up at 128 rows: 66 us against
-// 69 with 8 x 8 on 192 CUs).  int8 and Q4_0 steps take longer in the same proportion.
+// 69 with 8 x 8 on 192 CUs).  The shapes are compared within one weight type; an int8 step of
+// 12 x 8 tiles on all CUs takes 1.28 times a bf16 one, a Q4_0 step 1.45 times (gate/up of 144
+// rows 74.5, 95.6 and 108 us), which streaming_wins accounts for.
 // It picks, at the LLaDA-8B widths, 16 x 16 at 4096 rows, 12 x 16 for gate/up at 512
 // rows (256 workgroups in one round, 149 us; 16 x 16 fills 192 CUs: 166), 12 x 8 for
 // gate/up at 200 rows (86 us; 16 x 16: 168), K slices for O and down.

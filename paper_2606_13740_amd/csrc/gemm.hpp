@@ -120,10 +120,11 @@ constexpr int pipeline_depth() {
     // activations at a quarter to a sixteenth of that depth (activation_depth)
     if constexpr (F == 1 && (WT == WT_BF16 || WT == WT_I8)) return 16;
     if constexpr (WT == WT_Q4) {
-        // code stages: 8-byte codes + a scale dword per tile (3 VGPRs); the
+        // (one-tile groups and the LM head; the others run the fenced loop, which holds
+        // one chunk.)  Code stages: 8-byte codes + a scale dword per tile (3 VGPRs); the
         // activations have their own, shallower pipeline (activation_depth), so the
         // codes can run deeper: ~64 VGPRs of them up to 2 token tiles (an even count),
-        // ~36 at 3 and one stage at 4 token tiles
+        // ~36 at 3 and ~12 at 4 token tiles
         if constexpr (MT <= 2) {
             constexpr int d = 64 / (3 * F);
             return d < 2 ? 2 : (d > 8 ? 8 : (d & ~1));
@@ -142,11 +143,9 @@ constexpr int pipeline_depth() {
     return d < 1 ? 1 : (d > 8 ? 8 : d);
 }
 
-// Activation stages in flight: the weight depth, except for Q4_0 whose code
-// pipeline runs deeper than its activations (L2-resident, 16 dwords per token tile
-// and stage): one stage, which leaves the registers for 6 row tiles per wave
-// (LLaDA-8B gate/up at 32 rows: 23.6 us per launch against 33.5 with 3 tiles and
-// two activation stages); and bf16 at 3-4 token tiles (pipeline_depth).
+// Activation stages in flight: the weight depth, except for Q4_0 (one-tile groups and the
+// LM head) whose code pipeline runs deeper than its activations (L2-resident, 16 dwords
+// per token tile and stage), one stage; and bf16 at 3-4 token tiles (pipeline_depth).
 template <int WT, int F, int MT>
 constexpr int activation_depth() {
     if constexpr (WT == WT_Q4) return 1;
@@ -171,7 +170,9 @@ constexpr int activation_depth() {
 // without a memory access, so that no load stands behind a branch (behind one the compiler
 // cannot count the loads in flight and waits for nearly all of them); and a step's row
 // tiles are fenced from each other (left alone the scheduler unpacks all tiles first and
-// runs out of registers, which had kept gate/up and down at 3 tiles past 32 rows).  Us per
+// runs out of registers, which had kept gate/up and down at 3 tiles past 32 rows; gate/up's
+// 6 tiles at 4 token tiles still take all 256 and spill 12, and are no faster than 3: 50.7
+// against 49.7 us).  Us per
 // launch alone at the LLaDA-8B shapes (gate/up, QKV, down): 32 rows 24.2, 16.5, 15.3 ->
 // 22.0, 14.7, 13.5; 16 rows 19.7, 12.8, 11.6 -> 16.9, 11.5, 10.5; 48 rows 41.3, 21.5, 29.3
 // -> 27.8, 19.2, 17.5.  Three layers at 48 rows 377 -> 312 us.  One-tile O projections
@@ -238,12 +239,13 @@ gemm_kernel(GemmArgs g, Epi epi) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int wn = wave % NWn, wk = wave / NWn;
-    // Token blocks (grid.z > 1: windows of 65-512 rows).  The dispatcher deals
-    // consecutive workgroups to the 8 XCDs in turn; this mapping gives the z blocks
-    // of one row group consecutive slots on one XCD, so they run together and the
-    // group's weights come from HBM once and from that XCD's L2 after (LLaDA-8B
-    // gate/up at 512 rows: 270 against 358 us).  Past 8 blocks their activations
-    // no longer fit beside the weights and plain order is faster.
+    // Token blocks (grid.z > 1: past 64 rows, the LM head, fp32 models and the launches that
+    // stay here rather than in the tiled kernel).  The dispatcher deals consecutive
+    // workgroups to the 8 XCDs in turn; this mapping gives the z blocks of one row group
+    // consecutive slots on one XCD, so they run together and the group's weights come from
+    // HBM once and from that XCD's L2 after (bf16 LLaDA-8B gate/up, two blocks 77 against
+    // 92 us, eight 270 against 358).  Past 8 blocks their activations no longer fit beside
+    // the weights and plain order is faster.
     int bx = blockIdx.x, bz = blockIdx.z;
     if (gridDim.z > 1 && gridDim.z <= 8 && gridDim.y == 1 && (gridDim.x & 7) == 0) {
         const unsigned L = blockIdx.x + gridDim.x * blockIdx.z, j = L >> 3;
